@@ -244,6 +244,10 @@ cliff_status clifford_conv_nd_algo(int k, const int8_t* g, int64_t B, int64_t C_
         const cliff_status s = launch_linear_mfma(p, st);
         if (s != CLIFF_EUNSUPPORTED) return s;
     }
+    if (algo == CLIFF_ALGO_AUTO) {
+        const cliff_status s = launch_conv_split(p, st);
+        if (s != CLIFF_EUNSUPPORTED) return s;
+    }
     const cliff_status s = k == 1 ? launch_conv1d_mfma(p, st) : launch_conv_mfma(p, st);
     if (s != CLIFF_EUNSUPPORTED || mfma_forced) return s;
     return launch_conv_direct(p, st);

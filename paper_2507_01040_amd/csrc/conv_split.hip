@@ -1,0 +1,790 @@
+// k-D Clifford convolution (paper, Algorithm 1) on the bf16 matrix cores with
+// fp32 accuracy: every fp32 operand is the exact sum of three bf16 parts, and
+// every product of two operands six products of parts, summed in fp32 by
+// v_mfma_f32_32x32x16_bf16.
+//
+// Parts.  h = bf16(v), m = bf16(v - h), l = bf16(v - h - m), rounded to
+// nearest: v = h + m + l to the last bit.  The products h h, h m, m h, m m,
+// h l, l h are kept; those left out are below 2^-24 of the operands' product.
+//
+// Matrix form (REP).  Where the algebra is that of the 2 x 2 real (k = 2,
+// g = (1, 1), (1, -1), (-1, 1)) or complex matrices (k = 3, g = (1, 1, 1)),
+// filters and inputs are taken into matrix elements while they are staged
+// (one add per element) and the product of two multivectors is a matrix
+// product: N_B^2 / 2 real multiply-adds instead of N_B^2.  Row r of the
+// filter's matrix gives 32 MFMA rows (32 output channels), column c of the
+// input's 32 MFMA columns (32 positions), and the epilogue, where one lane
+// holds all elements of a (channel, position), returns to blades.  Other
+// signatures run the expanded kernel: row i is output blade i, and the K slots
+// of an input channel are its blades j with filter blade i ^ j and the table's
+// sign.
+//
+// Work decomposition.  P consecutive flattened output positions by CO_WG
+// output channels per workgroup.  The K loop runs over steps: one group of 16
+// K slots (16 / C input channels) of one filter tap.  The three parts of the
+// step's filters lie in an LDS ring of two slots, those of the input in two
+// buffers, one per stage (K group and row of filter taps: the taps of a row
+// read the same run of positions at a shift).  During a step each lane loads
+// the raw fp32 filters of the next step and a strip of the next stage's input,
+// converts them after the step's MFMAs and writes the parts to the other slot
+// and buffer; one barrier per step.
+//
+// Bound: the bf16 matrix cores at the clock their power allows.  A loop of
+// 32x32x16 MFMAs on random registers reaches 1793 TFLOP/s (2485 on zeros);
+// this kernel's MFMAs run at 1340 (k = 2, matrix form) to 1440 TFLOP/s (k = 3)
+// of it: without the staging (loads, conversions, LDS writes; a timing copy) a
+// step takes 10-14 % less, the rest is the barrier and the first fragments'
+// reads.  Measured against the fp32 tiles (start -> this kernel): k = 2, B 8,
+// C 64, d 128, 3x3 1077 -> 342 us; k = 3, B 8, C 32, d 32 5404 -> 1641 us;
+// block B 8, C 64, d 36 55.9 -> 16.4 ms; expanded kernel, g = (-1, -1), C 64,
+// d 128 1080 -> 594 us.  The error against 64 bits falls from 8.6e-7 to 5.2e-7
+// (2-norm, 2304 products), as 16 products go into one rounding.
+// Tried: 16x16x32 MFMAs with two products of parts in one (2055 TFLOP/s on
+// registers, but 28 instead of 18 KB of LDS reads a step and spills: 360 -> 428
+// us at k = 2), a third filter slot with fragments read ahead of the barrier
+// (335 -> 349 us), loads right after the conversions instead of at the start
+// of a step (360 -> 397 us), all taps of a row loaded at once (360 -> 369 us).
+//
+// Values that bf16 arithmetic cannot carry (infinities, sums past the largest
+// float) come out non-finite; such outputs are computed again, by the lane
+// that holds them, as plain fp32 sums.
+#include <stdio.h>
+
+#include <algorithm>
+#include <cmath>
+
+#include "common.hpp"
+#include "conv_split_geom.hpp"
+#include "epilogue.hpp"
+
+#ifndef CLIFF_SPLIT_VALU
+#define CLIFF_SPLIT_VALU 6
+#endif
+namespace cliff {
+namespace {
+
+typedef float f2 __attribute__((ext_vector_type(2)));
+typedef float f4 __attribute__((ext_vector_type(4)));
+typedef float f16 __attribute__((ext_vector_type(16)));
+typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+typedef __bf16 b8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+
+// The bf16 parts of two floats, packed (a in the low half).
+struct Parts {
+    uint32_t t[3];
+};
+__device__ inline uint32_t pack_bf16(float a, float b)
+{
+    const f2 v = {a, b};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, b2));
+}
+__device__ inline Parts split2(float a, float b)
+{
+    Parts p;
+    p.t[0] = pack_bf16(a, b);
+    const float a1 = a - __builtin_bit_cast(float, p.t[0] << 16);
+    const float b1 = b - __builtin_bit_cast(float, p.t[0] & 0xffff0000u);
+    p.t[1] = pack_bf16(a1, b1);
+    const float a2 = a1 - __builtin_bit_cast(float, p.t[1] << 16);
+    const float b2_ = b1 - __builtin_bit_cast(float, p.t[1] & 0xffff0000u);
+    p.t[2] = pack_bf16(a2, b2_);
+    return p;
+}
+
+// A multivector's matrix elements (REP).  k = 2: X = x0 + p sz + q sx + r e
+// with sz = diag(1, -1), sx = [[0, 1], [1, 0]], e = [[0, 1], [-1, 0]];
+// rep 0: g = (1, 1), (p, q, r) = (x1, x2, x12); rep 1: g = (1, -1), (x1, x12,
+// x2); rep 2: g = (-1, 1), (x2, -x12, x1).  M[row][column].
+__device__ inline void to_matrix(const float (&x)[4], int rep, float (&M)[4])
+{
+    const float p = rep == 2 ? x[2] : x[1];
+    const float r = rep == 0 ? x[3] : rep == 1 ? x[2] : x[1];
+    float q = rep == 0 ? x[2] : x[3];
+    q = rep == 2 ? -q : q;
+    M[0] = x[0] + p;
+    M[1] = q + r;
+    M[2] = q - r;
+    M[3] = x[0] - p;
+}
+__device__ inline void from_matrix(const float (&M)[4], int rep, float (&v)[8])
+{
+    const float p = 0.5f * (M[0] - M[3]), q = 0.5f * (M[1] + M[2]), r = 0.5f * (M[1] - M[2]);
+    v[0] = 0.5f * (M[0] + M[3]);
+    v[1] = rep == 2 ? r : p;
+    v[2] = rep == 0 ? q : rep == 1 ? r : p;
+    v[3] = rep == 0 ? r : rep == 1 ? q : -q;
+}
+// k = 3, g = (1, 1, 1): the Pauli matrices for e1, e2, e3.  M[2 * (2 * row +
+// column) + (0 real, 1 imaginary)].
+__device__ inline void to_matrix3(const float (&x)[8], float (&M)[8])
+{
+    M[0] = x[0] + x[3];
+    M[1] = x[7] + x[4];
+    M[2] = x[1] - x[5];
+    M[3] = x[6] - x[2];
+    M[4] = x[1] + x[5];
+    M[5] = x[6] + x[2];
+    M[6] = x[0] - x[3];
+    M[7] = x[7] - x[4];
+}
+__device__ inline void from_matrix3(const float (&M)[8], float (&v)[8])
+{
+    v[0] = 0.5f * (M[0] + M[6]);
+    v[3] = 0.5f * (M[0] - M[6]);
+    v[7] = 0.5f * (M[1] + M[7]);
+    v[4] = 0.5f * (M[1] - M[7]);
+    v[1] = 0.5f * (M[4] + M[2]);
+    v[5] = 0.5f * (M[4] - M[2]);
+    v[6] = 0.5f * (M[5] + M[3]);
+    v[2] = 0.5f * (M[5] - M[3]);
+}
+
+// One output multivector as plain fp32 sums.
+template <int KD, int NB>
+__device__ void plain_output(const SplitArgs& a, int m, int co, float (&v)[8])
+{
+    const int b = m / a.npos;
+    int p = m - b * a.npos;
+    int64_t off = 0, cs = 1;  // first input position, channel stride
+    int64_t st = 1;
+    for (int t = 0; t < KD; ++t) {
+        off += (int64_t)(p % a.Do) * st;
+        p /= a.Do;
+        st *= a.D;
+        cs *= a.D;
+    }
+    for (int i = 0; i < NB; ++i) v[i] = 0.f;
+    for (int ci = 0; ci < a.C_in; ++ci) {
+        const float* xb = a.x + (((int64_t)b * a.C_in + ci) * cs + off) * NB;
+        const float* wb = a.w + ((int64_t)ci * a.C_out + co) * a.taps * NB;
+        for (int q = 0; q < a.taps; ++q) {
+            int64_t qo = 0, qs = 1;
+            for (int t = 0, r = q; t < KD; ++t) {
+                qo += (int64_t)(r % a.df) * qs;
+                r /= a.df;
+                qs *= a.D;
+            }
+            for (int i = 0; i < NB; ++i)
+                for (int j = 0; j < NB; ++j)
+                    v[i] = fmaf(sign_of(a.sign, i * NB + j) * wb[q * NB + src_blade(NB, i, j)],
+                                xb[qo * NB + j], v[i]);
+            bool nan = true;
+            for (int i = 0; i < NB; ++i) nan = nan && v[i] != v[i];
+            if (nan) return;
+        }
+    }
+}
+
+template <int KD, int NB, int DF, int REP, int WCO, int WPOS, int NPT, int LP>
+__global__ __launch_bounds__(64 * WCO * WPOS, 2) void conv_split_kernel(SplitArgs a)
+{
+    constexpr SplitTile T{KD, NB, REP, WCO, WPOS, NPT, LP};
+    constexpr int R = T.R(), S = T.S(), C = T.C(), CHI = T.chi();
+    constexpr int NT = T.nt();
+    constexpr int NC = NPT * S;  // column tiles of a wave
+    constexpr int NXMAX = DF > 0 ? DF : 4;  // strip rounds of a stage
+
+    extern __shared__ u4 smem4[];
+    char* smem = reinterpret_cast<char*>(smem4);
+    char* const la = smem;
+    char* const lx = smem + 2 * T.a_bytes();
+
+    const SplitBlock g = split_block<KD>(T, a, blockIdx.x);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+    // conversion items of this lane: input strips (byte offset from the
+    // block's base, LDS byte), one filter item
+    const int xchi = split_x_chi(T, wave);
+    int xgoff[NXMAX], xlds[NXMAX];
+#pragma unroll
+    for (int j = 0; j < NXMAX; ++j) {
+        const int t = split_x_t(T, wave, lane, j);
+        xgoff[j] = j < a.nx ? split_x_goff<KD>(a, g, t) * (NB * 4) : 0;
+        xlds[j] = split_x_lds(T, xchi, t);
+    }
+    const bool a_on = T.a_items() >= NT || tid < T.a_items();
+    const int agoff = a_on ? split_a_goff(T, a, g, tid) * (NB * 4) : 0;
+    const int a_chan = a.C_out * a.taps * (NB * 4);  // bytes between input channels
+    char* const aw = la + split_a_lds(T, tid);
+    const float* const xbase = a.x + g.base * NB;
+
+    // K position of a stage: first channel of the group, tap row
+    struct Pos {
+        int ci0, rt;
+    };
+    // the next stage; after the last one the last again (loaded, never used)
+    auto next_stage = [&](const Pos& p) {
+        Pos q{p.ci0, p.rt + 1};
+        if (q.rt == a.nrt) {
+            q.rt = 0;
+            q.ci0 += T.cpg();
+        }
+        return q.ci0 < a.C_in ? q : p;
+    };
+
+    // Loads go through buffer descriptors: channels past C_in get an offset
+    // (or a size) that the hardware answers with zeros, without a branch.
+    auto load_mv = [&](__amdgpu_buffer_rsrc_t d, int off, int imm, float (&v)[NB]) {
+        if constexpr (NB == 2) {
+            const f2 q =
+                __builtin_bit_cast(f2, __builtin_amdgcn_raw_buffer_load_b64(d, off, imm, 0));
+            v[0] = q[0];
+            v[1] = q[1];
+        } else {
+#pragma unroll
+            for (int h = 0; h < NB / 4; ++h) {
+                const f4 q = __builtin_bit_cast(
+                    f4, __builtin_amdgcn_raw_buffer_load_b128(d, off + 16 * h, imm, 0));
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[4 * h + e] = q[e];
+            }
+        }
+    };
+    // raw filters of one step, `off` bytes from channel 0's first tap; the
+    // channels past C_in lie past the tensor's end
+    const __amdgpu_buffer_rsrc_t wdesc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float*>(a.w), (short)0, a.C_in * a_chan, 0x00020000);
+    auto load_a = [&](int off, float (&v)[CHI][NB]) {
+#pragma unroll
+        for (int c = 0; c < CHI; ++c) load_mv(wdesc, agoff + (off + c * a_chan), 0, v[c]);
+    };
+    auto write_slots = [&](char* p, const uint32_t* d) {  // CHI * C slots of one plane
+        if constexpr (CHI * C == 4)
+            *reinterpret_cast<u2*>(p) = u2{d[0], d[1]};
+        else
+            *reinterpret_cast<u4*>(p) = u4{d[0], d[1], d[2], d[3]};
+    };
+    auto store_a = [&](int slot, const float (&ra)[CHI][NB]) {
+        if (!a_on) return;
+        char* const p = aw + slot;
+        if constexpr (REP && NB == 4) {
+            float M[CHI][4];
+#pragma unroll
+            for (int c = 0; c < CHI; ++c) to_matrix(ra[c], a.rep, M[c]);
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                const Parts s0 = split2(M[0][2 * r], M[0][2 * r + 1]);
+                const Parts s1 = split2(M[1][2 * r], M[1][2 * r + 1]);
+#pragma unroll
+                for (int t = 0; t < 3; ++t) {
+                    const uint32_t d[2] = {s0.t[t], s1.t[t]};
+                    write_slots(p + split_a_plane(T, t, r, 0), d);
+                }
+            }
+        } else if constexpr (REP) {
+            float M[8];
+            to_matrix3(ra[0], M);
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                const Parts s0 = split2(M[4 * r], M[4 * r + 1]);
+                const Parts s1 = split2(M[4 * r + 2], M[4 * r + 3]);
+#pragma unroll
+                for (int t = 0; t < 3; ++t) {
+                    // (re, -im) for the real row, (im, re) for the imaginary one
+                    const uint32_t re[2] = {s0.t[t] ^ 0x80000000u, s1.t[t] ^ 0x80000000u};
+                    const uint32_t im[2] = {__builtin_amdgcn_alignbit(s0.t[t], s0.t[t], 16),
+                                            __builtin_amdgcn_alignbit(s1.t[t], s1.t[t], 16)};
+                    write_slots(p + split_a_plane(T, t, 2 * r, 0), re);
+                    write_slots(p + split_a_plane(T, t, 2 * r + 1, 0), im);
+                }
+            }
+        } else {
+            // K slots in bitmask order; row i takes blade i ^ j for slot j
+            constexpr int NP = NB / 2;
+            Parts s[CHI][NP];
+#pragma unroll
+            for (int c = 0; c < CHI; ++c)
+#pragma unroll
+                for (int h = 0; h < NP; ++h)
+                    s[c][h] = split2(ra[c][blade_perm(NB, 2 * h)], ra[c][blade_perm(NB, 2 * h + 1)]);
+#pragma unroll
+            for (int t = 0; t < 3; ++t)
+#pragma unroll
+                for (int i = 0; i < NB; ++i) {
+                    uint32_t d[CHI * NP];
+#pragma unroll
+                    for (int c = 0; c < CHI; ++c)
+#pragma unroll
+                        for (int h = 0; h < NP; ++h) {
+                            uint32_t v = s[c][h ^ (i >> 1)].t[t];
+                            if (i & 1) v = __builtin_amdgcn_alignbit(v, v, 16);
+                            d[c * NP + h] = (v ^ a.sx[i * NP + h]) & a.sz[i * NP + h];
+                        }
+                    write_slots(p + split_a_plane(T, t, i, 0), d);
+                }
+        }
+    };
+    // raw input of one strip of a stage (tap column 0); channels past C_in
+    // have a descriptor of size zero, which reads zeros
+    struct XDesc {
+        __amdgpu_buffer_rsrc_t d[CHI];
+    };
+    auto x_desc = [&](const Pos& p) {
+        XDesc r;
+        const int64_t rt = split_rt_off<KD>(a, p.rt);
+#pragma unroll
+        for (int c = 0; c < CHI; ++c) {
+            const int ci = p.ci0 + xchi * CHI + c;
+            const float* xs = xbase + ((int64_t)ci * a.cin_stride + rt) * NB;
+            r.d[c] = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(xs), (short)0,
+                                                       ci < a.C_in ? 0x7fffffff : 0, 0x00020000);
+        }
+        return r;
+    };
+    auto load_x = [&](const XDesc& r, int goff, float (&v)[CHI][NB]) {
+#pragma unroll
+        for (int c = 0; c < CHI; ++c) load_mv(r.d[c], goff, 0, v[c]);
+    };
+    auto store_x = [&](int buf, int lds, bool on, const float (&v)[CHI][NB]) {
+        if (!on) return;
+        char* const p = lx + buf + lds;
+        if constexpr (REP && NB == 4) {
+            float M[CHI][4];
+#pragma unroll
+            for (int c = 0; c < CHI; ++c) to_matrix(v[c], a.rep, M[c]);
+#pragma unroll
+            for (int col = 0; col < 2; ++col) {
+                const Parts s0 = split2(M[0][col], M[0][2 + col]);
+                const Parts s1 = split2(M[1][col], M[1][2 + col]);
+#pragma unroll
+                for (int t3 = 0; t3 < 3; ++t3) {
+                    const uint32_t d[2] = {s0.t[t3], s1.t[t3]};
+                    write_slots(p + split_x_plane(T, t3, col, 0), d);
+                }
+            }
+        } else if constexpr (REP) {
+            float M[8];
+            to_matrix3(v[0], M);
+#pragma unroll
+            for (int col = 0; col < 2; ++col) {
+                const Parts s0 = split2(M[2 * col], M[2 * col + 1]);
+                const Parts s1 = split2(M[4 + 2 * col], M[5 + 2 * col]);
+#pragma unroll
+                for (int t3 = 0; t3 < 3; ++t3) {
+                    const uint32_t d[2] = {s0.t[t3], s1.t[t3]};
+                    write_slots(p + split_x_plane(T, t3, col, 0), d);
+                }
+            }
+        } else {
+            constexpr int NP = NB / 2;
+            Parts s[CHI * NP];
+#pragma unroll
+            for (int c = 0; c < CHI; ++c)
+#pragma unroll
+                for (int h = 0; h < NP; ++h)
+                    s[c * NP + h] =
+                        split2(v[c][blade_perm(NB, 2 * h)], v[c][blade_perm(NB, 2 * h + 1)]);
+#pragma unroll
+            for (int t3 = 0; t3 < 3; ++t3) {
+                uint32_t d[CHI * NP];
+#pragma unroll
+                for (int h = 0; h < CHI * NP; ++h) d[h] = s[h].t[t3];
+                write_slots(p + split_x_plane(T, t3, 0, 0), d);
+            }
+        }
+    };
+
+    f16 acc[R][NC];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int n = 0; n < NC; ++n)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[r][n][e] = 0.f;
+
+    const char* const fa0 = la + split_a_frag(T, wave, lane);
+    const char* fb0[NPT];
+#pragma unroll
+    for (int np = 0; np < NPT; ++np) fb0[np] = lx + split_b_frag(T, a, g, wave, lane, np);
+
+    auto frag = [&](const char* p) { return *reinterpret_cast<const b8*>(p); };
+    // The six products of parts, smallest first.
+    constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
+    // One step's MFMAs, in regions of one streamed fragment (a column tile's,
+    // or a row's) by all held ones.  Within a region the next fragment's LDS
+    // reads are spread between the MFMAs; `load()`, the next step's global
+    // loads, goes behind the first fragments' reads, and `convert(0)` and
+    // `convert(1)`, the vector work on them, between the MFMAs of the last two
+    // regions.
+    constexpr bool HOLD_A = R <= NC;
+    constexpr int NH = HOLD_A ? R : NC, NS = HOLD_A ? NC : R;
+    auto compute = [&](int slot, int off, auto load, auto convert) {
+        auto rd_a = [&](int r, int t) { return frag(fa0 + slot + split_a_plane(T, t, r, 0)); };
+        auto rd_b = [&](int n, int t) {
+            return frag(fb0[n / S] + off + split_x_plane(T, t, n % S, 0));
+        };
+        b8 H[NH][3], F[2][3];
+#pragma unroll
+        for (int t = 2; t >= 0; --t) {
+#pragma unroll
+            for (int h = 0; h < NH; ++h) H[h][t] = HOLD_A ? rd_a(h, t) : rd_b(h, t);
+            F[0][2 - t] = HOLD_A ? rd_b(0, 2 - t) : rd_a(0, 2 - t);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        load();
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int n = 0; n < NS; ++n) {
+            constexpr int NM = 6 * NH;
+            if (n + 1 < NS) {
+#pragma unroll
+                for (int t = 0; t < 3; ++t)
+                    F[(n + 1) & 1][t] = HOLD_A ? rd_b(n + 1, t) : rd_a(n + 1, t);
+            }
+            if (n == NS - 2) convert(0);
+            if (n == NS - 1) convert(1);
+#pragma unroll
+            for (int q = 0; q < 6; ++q)
+#pragma unroll
+                for (int h = 0; h < NH; ++h) {
+                    if constexpr (HOLD_A)
+                        acc[h][n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                            H[h][PA[q]], F[n & 1][PB[q]], acc[h][n], 0, 0, 0);
+                    else
+                        acc[n][h] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                            F[n & 1][PB[q]], H[h][PA[q]], acc[n][h], 0, 0, 0);
+                }
+            const int nrd = n + 1 < NS ? 3 : 0;
+#pragma unroll
+            for (int i = 0; i < NM; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                if (i < nrd) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                else if (n >= NS - 2) __builtin_amdgcn_sched_group_barrier(0x002, CLIFF_SPLIT_VALU, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    // Strips past the LP positions of a buffer are loaded but not kept.
+    auto x_on = [&](int j) {
+        constexpr int PER = T.waves() / T.nchi() * 64;
+        return (j + 1) * PER <= LP || split_x_t(T, wave, lane, j) < LP;
+    };
+    float ra[CHI][NB], rx[CHI][NB];
+
+    // Filters of the first step, input of the first stage.
+    constexpr int AB = T.a_bytes(), XB = T.x_bytes();
+    const int df = DF > 0 ? DF : a.df;
+    const int n_stage = a.n_step / df;
+    Pos cur{0, 0};
+    load_a(0, ra);
+    {
+        const XDesc d = x_desc(cur);
+#pragma unroll
+        for (int j = 0; j < NXMAX; ++j)
+            if (j < a.nx) {
+                load_x(d, xgoff[j], rx);
+                store_x(0, xlds[j], x_on(j), rx);
+            }
+    }
+    store_a(0, ra);
+    __syncthreads();
+
+    int slot = 0;
+    for (int st = 0; st < n_stage; ++st) {
+        // (behind the last step, its filters and input are loaded again and
+        // written where nothing reads them)
+        const Pos nst = next_stage(cur);
+        const XDesc xd = x_desc(nst);
+        const int xb = (st & 1) * XB, xn = XB - xb;
+        const int w_cur = cur.ci0 * a_chan + cur.rt * df * (NB * 4);
+        const int w_nxt = nst.ci0 * a_chan + nst.rt * df * (NB * 4);
+        auto step = [&](int qx) {
+            const int wo = qx + 1 < df ? w_cur + (qx + 1) * (NB * 4) : w_nxt;
+            if constexpr (DF > 0) {
+                compute(slot, xb + qx * 16,
+                        [&]() {
+                            load_a(wo, ra);
+                            load_x(xd, xgoff[qx], rx);
+                        },
+                        [&](int half) {
+                            if (half == 0) store_a(AB - slot, ra);
+                            else store_x(xn, xlds[qx], x_on(qx), rx);
+                        });
+            } else {
+                // strip rounds qx xi ... of the next stage, the first of them
+                // loaded with the filters
+                compute(slot, xb + qx * 16,
+                        [&]() {
+                            load_a(wo, ra);
+#pragma unroll
+                            for (int j = 0; j < NXMAX; ++j)
+                                if (j == qx * a.xi && j < a.nx) load_x(xd, xgoff[j], rx);
+                        },
+                        [&](int half) {
+                            if (half == 1) store_a(AB - slot, ra);
+                        });
+#pragma unroll
+                for (int j = 0; j < NXMAX; ++j)
+                    if (j >= qx * a.xi && j < (qx + 1) * a.xi && j < a.nx) {
+                        if (j > qx * a.xi) load_x(xd, xgoff[j], rx);
+                        store_x(xn, xlds[j], x_on(j), rx);
+                    }
+            }
+            __syncthreads();
+            slot = AB - slot;
+        };
+        if constexpr (DF > 0) {
+#pragma unroll
+            for (int qx = 0; qx < DF; ++qx) step(qx);
+        } else {
+            for (int qx = 0; qx < df; ++qx) step(qx);
+        }
+        cur = nst;
+    }
+
+    // Epilogue: back to blades, bias, optional activation; one lane holds a
+    // whole multivector.
+    const bool has_act = a.act.mode >= 0;
+    int gslot[NB];
+#pragma unroll
+    for (int i = 0; i < NB; ++i) gslot[i] = has_act ? gate_slot(a.act, i) : -1;
+    const FastDiv fnpos = fast_div(a.npos);
+    auto finish = [&](float (&v)[8], int m, int co) {
+        if (a.bias) {
+#pragma unroll
+            for (int i = 0; i < NB; ++i) v[i] += a.bias[co * NB + i];
+        }
+        if (has_act) {
+            float part = 0.f;
+#pragma unroll
+            for (int i = 0; i < NB; ++i) part += gate_coef(a.act, gslot[i], co) * v[i];
+            const float gate = gate_sigmoid(a.act, part, co);
+#pragma unroll
+            for (int i = 0; i < NB; ++i) v[i] *= gate;
+        }
+        float* const yp = a.y + split_out_ofs(a, fnpos, m, co) * NB;
+        if constexpr (NB == 2) {
+            *reinterpret_cast<f2*>(yp) = f2{v[0], v[1]};
+        } else {
+#pragma unroll
+            for (int h = 0; h < NB / 4; ++h)
+                reinterpret_cast<f4*>(yp)[h] = f4{v[4 * h], v[4 * h + 1], v[4 * h + 2], v[4 * h + 3]};
+        }
+    };
+    uint32_t bad[NPT];
+#pragma unroll
+    for (int np = 0; np < NPT; ++np) {
+        const int m = split_out_m(T, g, wave, lane, np);
+        bad[np] = 0;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const int co = split_out_co(T, g, wave, lane, e);
+            float v[8];
+            if constexpr (REP && NB == 4) {
+                const float M[4] = {acc[0][np * 2][e], acc[0][np * 2 + 1][e], acc[1][np * 2][e],
+                                    acc[1][np * 2 + 1][e]};
+                from_matrix(M, a.rep, v);
+            } else if constexpr (REP) {
+                float M[8];
+#pragma unroll
+                for (int r = 0; r < 2; ++r)
+#pragma unroll
+                    for (int c = 0; c < 2; ++c)
+#pragma unroll
+                        for (int ri = 0; ri < 2; ++ri)
+                            M[2 * (2 * r + c) + ri] = acc[2 * r + ri][np * 2 + c][e];
+                from_matrix3(M, v);
+            } else {
+#pragma unroll
+                for (int i = 0; i < NB; ++i) v[blade_perm(NB, i)] = acc[i][np][e];
+            }
+            if (m < g.m_end && co < a.C_out) {
+                float z = 0.f;
+#pragma unroll
+                for (int i = 0; i < NB; ++i) z = fmaf(v[i], 0.f, z);
+                if (z != 0.f) bad[np] |= 1u << e;  // a blade is infinite or NaN
+                finish(v, m, co);
+            }
+        }
+    }
+#pragma unroll
+    for (int np = 0; np < NPT; ++np) {
+        const int m = split_out_m(T, g, wave, lane, np);
+        while (bad[np]) {
+            const int e = __builtin_ctz(bad[np]);
+            bad[np] &= bad[np] - 1;
+            const int co = split_out_co(T, g, wave, lane, e);
+            float v[8];
+            plain_output<KD, NB>(a, m, co, v);
+            finish(v, m, co);
+        }
+    }
+}
+
+template <int KD, int NB, int DF, int REP, int WCO, int WPOS, int NPT, int LP>
+cliff_status run(const ConvProblem& p, hipStream_t stream, int64_t* blocks)
+{
+    constexpr SplitTile T{KD, NB, REP, WCO, WPOS, NPT, LP};
+    static_assert(T.lds_bytes() <= 160 * 1024, "LDS");
+    const int64_t D = p.d_image, Do = p.d_out, df = p.d_filter, P = T.pos();
+    int64_t npos = 1, img = 1, taps = 1;
+    for (int t = 0; t < KD; ++t) {
+        npos *= Do;
+        img *= D;
+        taps *= df;
+    }
+    const int64_t M = p.B * npos;
+    // 32-bit position indices; input offsets are 32-bit multivector counts
+    // from the block's first row, which spans at most `rows` output rows
+    const int64_t cross = (P - 1 + Do - 1) / Do, rows = cross + 1;
+    const int64_t entries = KD == 1 ? rows : rows / (npos / Do) + 2;
+    // and, like those of the filters, 31-bit byte offsets
+    if (M >= (1ll << 31) - P || (entries + 1) * p.C_in * img * NB * 4 >= (1ll << 31) ||
+        (p.C_in + T.cpg()) * p.C_out * taps * NB * 4 >= (1ll << 31))
+        return CLIFF_EUNSUPPORTED;
+    // the longest run of input positions of a block
+    const int64_t L = P + (cross + 1) * (df - 1);
+    constexpr int per_round = T.waves() / T.nchi() * 64;
+    const int64_t nx = (L + per_round - 1) / per_round;
+    const int64_t xi = (nx + df - 1) / df;
+    if (L > LP || nx > (DF > 0 ? DF : 4) || xi > (DF > 0 ? 1 : 2)) return CLIFF_EUNSUPPORTED;
+    const int64_t n_co_blk = (p.C_out + T.co_wg() - 1) / T.co_wg();
+    const int64_t n_blk = (M + P - 1) / P * n_co_blk;
+    const int64_t n_grp = (p.C_in + T.cpg() - 1) / T.cpg();
+    if (n_blk >= (1ll << 31) || n_grp * taps >= (1ll << 31)) return CLIFF_EUNSUPPORTED;
+    if (blocks) {  // a plan only
+        *blocks = n_blk;
+        return CLIFF_OK;
+    }
+
+    SplitArgs a;
+    a.x = p.x;
+    a.w = p.w;
+    a.bias = p.bias;
+    a.y = p.y;
+    a.C_in = (int)p.C_in;
+    a.C_out = (int)p.C_out;
+    a.D = (int)D;
+    a.Do = (int)Do;
+    a.df = (int)df;
+    a.M = (int)M;
+    a.npos = (int)npos;
+    a.nrow = (int)(M / Do);
+    a.taps = (int)taps;
+    a.nrt = (int)(taps / df);
+    a.n_step = (int)(n_grp * taps);
+    a.n_co_blk = (int)n_co_blk;
+    a.n_blk = (int)n_blk;
+    a.nx = (int)nx;
+    a.xi = (int)xi;
+    a.cin_stride = (int)img;
+    a.rep = KD == 2 ? split_rep2(p.sign) : 0;
+    a.sign = p.sign;
+    a.act = p.act;
+    for (int i = 0; i < NB; ++i)
+        for (int h = 0; h < NB / 2; ++h) {
+            uint32_t sx = 0, sz = 0;
+            for (int e = 0; e < 2; ++e) {
+                const float s = sign_of(p.sign, blade_perm(NB, i) * NB + blade_perm(NB, 2 * h + e));
+                sx |= (s < 0.f ? 0x8000u : 0u) << (16 * e);
+                sz |= (s != 0.f ? 0xffffu : 0u) << (16 * e);
+            }
+            a.sx[i * (NB / 2) + h] = sx;
+            a.sz[i * (NB / 2) + h] = sz;
+        }
+    if (debug_enabled())
+        fprintf(stderr,
+                "cliffconv: conv_split k=%d d_filter=%d %s, %d channels x %d positions, "
+                "%lld workgroups of %d, %d LDS bytes\n",
+                KD, (int)df, REP ? "matrices" : "blades", T.co_wg(), (int)P, (long long)n_blk,
+                T.nt(), T.lds_bytes());
+    if (observe_launch(LAUNCH_CONV_SPLIT, {KD, NB, REP, WCO, WPOS, NPT, LP}, n_blk, T.nt(),
+                       T.lds_bytes(), &a))
+        return CLIFF_OK;
+    clear_hip_error();
+    hipLaunchKernelGGL((conv_split_kernel<KD, NB, DF, REP, WCO, WPOS, NPT, LP>), dim3((unsigned)n_blk),
+                       dim3(T.nt()), (size_t)T.lds_bytes(), stream, a);
+    return hipGetLastError() == hipSuccess ? CLIFF_OK : CLIFF_EDEVICE;
+}
+
+// One tile shape: its launcher (or planner), and the microseconds of one step
+// (one K group of one tap, at 3 taps a row) with one and with two workgroups
+// on every CU, measured on MI355X at 256 and 512 workgroups (8-wave workgroups
+// fill a CU alone).
+struct Shape {
+    cliff_status (*run)(const ConvProblem&, hipStream_t, int64_t*);
+    int cpg;
+    double t1, t2;
+};
+template <int KD, int NB, int DF, int REP, int WCO, int WPOS, int NPT, int LP>
+constexpr Shape shape(double t1, double t2)
+{
+    return Shape{run<KD, NB, DF, REP, WCO, WPOS, NPT, LP>,
+                 SplitTile{KD, NB, REP, WCO, WPOS, NPT, LP}.cpg(), t1, t2};
+}
+
+template <int DF>
+cliff_status launch_df(const ConvProblem& p, hipStream_t stream, double most_us)
+{
+    // 64 x 256, 64 x 128, 32 x 256, 32 x 128 (channels x positions; 64 x 64
+    // measured 1.20, 1.70: never ahead of 32 x 128)
+    static constexpr Shape rep2[] = {
+        shape<2, 4, DF, 1, 2, 4, 2, 320>(2.43, 4.70), shape<2, 4, DF, 1, 2, 2, 2, 148>(1.55, 2.60),
+        shape<2, 4, DF, 1, 1, 8, 1, 320>(1.47, 2.79), shape<2, 4, DF, 1, 1, 4, 1, 148>(1.18, 1.61)};
+    // ... and 64 x 64
+    static constexpr Shape gen2[] = {
+        shape<2, 4, DF, 0, 2, 4, 2, 320>(2.13, 4.18), shape<2, 4, DF, 0, 2, 2, 2, 168>(1.19, 2.23),
+        shape<2, 4, DF, 0, 1, 8, 1, 320>(1.12, 2.20), shape<2, 4, DF, 0, 1, 4, 1, 168>(0.76, 1.27),
+        shape<2, 4, DF, 0, 2, 2, 1, 100>(0.75, 1.36)};
+    // 32 x 128, 64 x 64, 64 x 128
+    static constexpr Shape rep3[] = {shape<3, 8, DF, 1, 1, 4, 1, 148>(1.23, 2.27),
+                                     shape<3, 8, DF, 1, 2, 2, 1, 84>(1.25, 2.32),
+                                     shape<3, 8, DF, 1, 2, 4, 1, 288>(2.12, 4.17)};
+    // 32 x 128, 32 x 256
+    static constexpr Shape gen3[] = {shape<3, 8, DF, 0, 1, 4, 1, 168>(1.48, 2.28),
+                                     shape<3, 8, DF, 0, 1, 8, 1, 320>(2.10, 4.17)};
+    const Shape* s;
+    int n;
+    if (p.k == 2) {
+        const bool rep = split_rep2(p.sign) >= 0;
+        s = rep ? rep2 : gen2;
+        n = rep ? 4 : 5;
+    } else if (split_rep3(p.sign)) {
+        s = rep3;
+        n = 3;
+    } else {
+        s = gen3;
+        n = 2;
+    }
+    const int cus = device_cus();
+    if (cus < 1) return CLIFF_EUNSUPPORTED;
+    // Estimate: the CU with the most workgroups takes them in pairs; a step
+    // with `df` taps a row converts 1 / df of a stage's input (fitted at 3 and
+    // 5 taps); 5 us of launch, prologue and epilogue.
+    const double df = (double)p.d_filter;
+    const Shape* best = nullptr;
+    double best_us = most_us;
+    for (int i = 0; i < n; ++i) {
+        int64_t blocks = 0;
+        if (s[i].run(p, stream, &blocks) != CLIFF_OK) continue;
+        const int64_t w = (blocks + cus - 1) / cus;
+        const double steps = (double)((p.C_in + s[i].cpg - 1) / s[i].cpg) * std::pow(df, p.k);
+        const double us = 5.0 + steps * (0.67 + 1.0 / df) *
+                                    ((double)(w / 2) * s[i].t2 + (double)(w % 2) * s[i].t1);
+        if (us < best_us) {
+            best_us = us;
+            best = &s[i];
+        }
+    }
+    return best ? best->run(p, stream, nullptr) : CLIFF_EUNSUPPORTED;
+}
+
+}  // namespace
+
+cliff_status launch_conv_split(const ConvProblem& p, hipStream_t stream)
+{
+    if (launch_observer && launch_observer->last_kind < LAUNCH_CONV_SPLIT) return CLIFF_EUNSUPPORTED;
+    if (p.k < 2 || p.d_filter < 2) return CLIFF_EUNSUPPORTED;
+    // Taken where the estimate is below the time of the fp32 tiles at their
+    // best rate (146 TFLOP/s, 0.93 of the fp32 peak, on the largest layers);
+    // smaller layers, where that rate is out of reach for either, stay there.
+    double useful = 2.0 * (double)p.B * p.C_out * p.C_in * p.nb * p.nb;
+    for (int t = 0; t < p.k; ++t) useful *= (double)p.d_out * p.d_filter;
+    const double most_us = useful / 146e6;
+    return p.d_filter == 3 ? launch_df<3>(p, stream, most_us) : launch_df<0>(p, stream, most_us);
+}
+
+}  // namespace cliff

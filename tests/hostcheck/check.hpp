@@ -46,6 +46,7 @@ void check_block_small(const cliff::LaunchPlan& p);
 void check_act(const cliff::LaunchPlan& p);
 void check_linear(const cliff::LaunchPlan& p);
 void check_direct(const cliff::LaunchPlan& p);
+void check_conv_split(const cliff::LaunchPlan& p);
 void check_generic(const cliff::LaunchPlan& p);
 
 }  // namespace hostcheck

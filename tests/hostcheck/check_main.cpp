@@ -18,6 +18,7 @@
 //   conv   k g_1..g_k B C_in C_out d_image d_filter algo  ACT
 //   block  k g_1..g_k B C_in C_mid C_out d_image d_filter path  ACT ACT
 //   act    nb B C P  ACT
+//   kinds  n  (the highest LaunchKind the cases after it may launch)
 //   fastdiv  (the reciprocal division of the kernels' index arithmetic)
 // with ACT = mode K blade_1..blade_K (mode -1: none, K then 0).
 // Output: one line per case, "ok <status> <launches> <simulated workgroups>
@@ -93,6 +94,7 @@ static void on_launch(const cliff::LaunchPlan& p, void*)
     case cliff::LAUNCH_ACT: check_act(p); break;
     case cliff::LAUNCH_LINEAR_MFMA: check_linear(p); break;
     case cliff::LAUNCH_CONV_DIRECT: check_direct(p); break;
+    case cliff::LAUNCH_CONV_SPLIT: check_conv_split(p); break;
     default: check_generic(p); break;
     }
 }
@@ -204,6 +206,9 @@ int main()
                                              a1.on ? &a1.d : nullptr, w2, b2,
                                              a2.on ? &a2.d : nullptr, ws, y, nullptr, path);
             }
+        } else if (kind == "kinds") {
+            in >> obs.last_kind;
+            st = 0;
         } else if (kind == "fastdiv") {
             // the kernels' division by a reciprocal (conv_mfma_geom.hpp)
             // against integer division: every n below 2^20 for d below 64,

@@ -1,0 +1,129 @@
+"""GPU parity of the split-operand convolution kernel (bf16 matrix cores, every
+fp32 operand the sum of three parts), through the automatic choice on layers
+that take it: matrix form and expanded form, every tile shape, ragged channels
+and positions, filter lengths with and without an unrolled kernel, gates, no
+bias.  The host bounds checker walks the same launches and asserts their tiles
+(tests/test_split_bounds.py).
+
+Tolerance: a sum of n products in fp32, in any order, rounds to about
+2^-24 sqrt(n) of the largest outputs (random signs, unit-variance terms); twice
+that, and the fp32 kernel's own error on the same layer may not be less than a
+third of it."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2507_01040_amd as P
+import workloads as W
+from gpu_util import dev, normwise
+
+pytestmark = pytest.mark.gpu
+
+LIN, SUM, MEAN = P.AGG_LINEAR, P.AGG_SUM, P.AGG_MEAN
+# (g, (B, C_in, C_out, d_image, d_filter), gate (mode, blades) or None, bias,
+#  tile REP.WCO.WPOS.NPT)
+CASES = [
+    ((1, 1), (4, 9, 62, 130, 3), None, True, "1.2.4.2"),
+    ((1, 1), (1, 8, 64, 300, 3), (LIN, (0, 1, 2, 3)), True, "1.2.2.2"),
+    ((1, -1), (3, 13, 61, 93, 3), None, False, "1.1.8.1"),
+    ((-1, 1), (1, 24, 64, 128, 3), (MEAN, (3,)), True, "1.1.4.1"),
+    ((-1, 1), (6, 16, 32, 67, 7), (LIN, (1, 3)), True, "1.1.8.1"),
+    ((1, 1), (7, 16, 64, 98, 2), (SUM, (2, 1)), True, "1.2.2.2"),
+    ((1, -1), (6, 13, 61, 90, 5), None, False, "1.2.4.2"),
+    ((-1, 0), (4, 9, 62, 127, 3), (MEAN, (0, 2)), True, "0.2.4.2"),
+    ((-1, -1), (1, 24, 64, 128, 3), None, True, "0.2.2.1"),
+    ((0, 1), (1, 8, 64, 300, 3), (LIN, (3, 0, 1)), True, "0.1.8.1"),
+    ((-1, -1), (6, 13, 61, 90, 5), None, False, "0.1.4.1"),
+    ((1, 1, 1), (2, 16, 32, 26, 3), (MEAN, tuple(range(8))), True, "1.1.4.1"),
+    ((1, 1, 1), (40, 8, 29, 12, 3), (LIN, (7, 0, 3)), True, "1.2.2.1"),
+    ((1, 1, 1), (64, 7, 60, 10, 3), None, False, "1.2.4.1"),
+    ((1, -1, 1), (8, 6, 20, 34, 3), None, True, "0.1.8.1"),
+    ((0, 0, 1), (64, 7, 60, 10, 3), (SUM, (4, 1)), True, "0.1.4.1"),
+]
+IDS = ["%s-%s" % ("".join(str(v) for v in g), "x".join(str(v) for v in s)) for g, s, _, _, _ in CASES]
+
+
+def _inputs(g, shape, gate, bias, seed):
+    B, C_in, C_out, d, df = shape
+    _, x, f, b = W.random_conv_case(seed, len(g), g, B, C_in, C_out, d, df, bias_std=0.1)
+    act = None
+    if gate is not None:
+        rng = np.random.default_rng(seed + 1)
+        mode, blades = gate
+        aw = rng.standard_normal((C_out, len(blades))).astype(np.float32) if mode == LIN else None
+        ab = (0.1 * rng.standard_normal(C_out)).astype(np.float32) if mode == LIN else None
+        act = (mode, blades, aw, ab)
+    return x, f, (b if bias else None), act
+
+
+def _run(g, x, f, b, act, algo):
+    a = None if act is None else (act[0], act[1], None if act[2] is None else dev(act[2]),
+                                  None if act[3] is None else dev(act[3]))
+    k = len(g)
+    d_out = x.shape[2] - f.shape[2] + 1
+    y = torch.full((x.shape[0], f.shape[1]) + (d_out,) * k + (1 << k,), float("nan"),
+                   dtype=torch.float32, device="cuda:0")
+    P.conv_nd(dev(x), dev(f), None if b is None else dev(b), g, act=a, out=y, algo=algo)
+    torch.cuda.synchronize()
+    return y.cpu().numpy()
+
+
+@pytest.mark.parametrize("case", CASES, ids=IDS)
+def test_conv_split(case):
+    g, shape, gate, bias, _ = case
+    print(g, shape, gate, flush=True)
+    x, f, b, act = _inputs(g, shape, gate, bias, 4000 + sum(shape))
+    y = _run(g, x, f, b, act, P.ALGO_AUTO)
+    assert np.isfinite(y).all()
+    z = _run(g, x, f, b, act, P.ALGO_MFMA)
+    assert not np.array_equal(y, z)  # not the fp32 kernels' result
+    sel = sorted({0, shape[0] - 1})
+    ref = oracle.conv_nd(x[sel], f, np.zeros((shape[2], 1 << len(g)), np.float32) if b is None else b, g)
+    if act is not None:
+        ref = oracle.act(ref, *act)
+    n = shape[1] * (1 << len(g)) * shape[4] ** len(g)
+    e, ez = normwise(y[sel], ref), normwise(z[sel], ref)
+    print("normwise %.2e, fp32 kernel %.2e" % (e, ez), flush=True)
+    assert e <= 2.0 ** -23 * np.sqrt(n)
+    assert e <= 3 * ez
+
+
+@pytest.mark.parametrize("g", [(1, 1), (-1, 0), (1, 1, 1), (1, -1, 1)], ids=str)
+def test_conv_split_non_finite(g):
+    # infinities, NaN, the largest floats and products past them: outputs that
+    # bf16 parts or sums of matrix elements cannot hold are those of the
+    # vector kernel, the others are untouched
+    k = len(g)
+    shape = (1, 8, 64, 300, 3) if k == 2 else (2, 16, 32, 26, 3)
+    x, f, b, _ = _inputs(g, shape, None, True, 77)
+    big = np.float32(3.3e38)
+    x[(0, 3) + (4,) * k] = np.inf
+    x[(0, 2) + (9,) * k + (1,)] = np.nan
+    x[(0, 1) + (14,) * k] = big            # sums of blades overflow, outputs do not
+    x[(0, 4) + (20,) * k + (0,)] = -np.inf
+    f[(0, 5) + (1,) * k] = 0.0              # zero filter against the values above
+    f[(3, 6) + (0,) * k + (1,)] = 0.0
+    # products past the largest float, one to an output (sums of several could
+    # pass it in one order and not in another)
+    f[(1, 9) + (2,) * k] = 0.0
+    f[(1, 9) + (2,) * k + (0,)] = big
+    y = _run(g, x, f, b, None, P.ALGO_AUTO)
+    r = _run(g, x, f, b, None, P.ALGO_DIRECT)
+    fin = np.isfinite(r)
+    assert (~fin).any() and fin.any() and np.isposinf(r).any() and np.isnan(r).any()
+    np.testing.assert_array_equal(np.isfinite(y), fin)
+    np.testing.assert_array_equal(np.isnan(y), np.isnan(r))
+    np.testing.assert_array_equal(y[np.isinf(r)], r[np.isinf(r)])
+    huge = fin & (np.abs(r) > 1e30)
+    assert huge.any()
+    # a sum of up to n terms of size T rounds to 2^-24 n T; the terms of these
+    # outputs are up to the largest float times the largest filter
+    T = float(big) * max(1.0, float(np.abs(f[np.abs(f) < 1e30]).max()))
+    assert np.max(np.abs(y[huge].astype(np.float64) - r[huge])) <= 2.0 ** -20 * T
+    ok = fin & (np.abs(r) <= 1e30)
+    # the others: as in test_conv_split, next to outputs of the usual size
+    n = shape[1] * (1 << k) * 3 ** k
+    usual = ok & (np.abs(r) < 1e3)
+    assert np.max(np.abs(y[usual].astype(np.float64) - r[usual])) <= \
+        2.0 ** -22 * np.sqrt(n) * np.max(np.abs(r[usual]))
