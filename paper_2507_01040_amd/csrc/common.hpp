@@ -103,6 +103,7 @@ enum LaunchKind {
     LAUNCH_BLOCK_SMALL,
     LAUNCH_ACT,
     LAUNCH_CONV_SPLIT,
+    LAUNCH_LINEAR_SPLIT,
 };
 struct LaunchPlan {
     int kind;
@@ -148,6 +149,8 @@ cliff_status launch_conv_split(const ConvProblem& p, hipStream_t stream);
 // Linear layers (d_image = d_filter = 1) on the streamed MFMA kernel;
 // CLIFF_EUNSUPPORTED without launching when the channel counts do not fit it.
 cliff_status launch_linear_mfma(const ConvProblem& p, hipStream_t stream);
+// The same layers on the bf16 matrix cores with split operands; likewise.
+cliff_status launch_linear_split(const ConvProblem& p, hipStream_t stream);
 // The fused small-block kernel; CLIFF_EUNSUPPORTED without launching when its
 // LDS working set does not fit.
 cliff_status launch_block_small(const BlockProblem& p, hipStream_t stream);

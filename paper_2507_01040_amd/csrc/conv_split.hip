@@ -56,6 +56,7 @@
 #include "common.hpp"
 #include "conv_split_geom.hpp"
 #include "epilogue.hpp"
+#include "split.hpp"
 
 #ifndef CLIFF_SPLIT_VALU
 #define CLIFF_SPLIT_VALU 6
@@ -66,32 +67,9 @@ namespace {
 typedef float f2 __attribute__((ext_vector_type(2)));
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef float f16 __attribute__((ext_vector_type(16)));
-typedef __bf16 b2 __attribute__((ext_vector_type(2)));
 typedef __bf16 b8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u4 __attribute__((ext_vector_type(4)));
-
-// The bf16 parts of two floats, packed (a in the low half).
-struct Parts {
-    uint32_t t[3];
-};
-__device__ inline uint32_t pack_bf16(float a, float b)
-{
-    const f2 v = {a, b};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, b2));
-}
-__device__ inline Parts split2(float a, float b)
-{
-    Parts p;
-    p.t[0] = pack_bf16(a, b);
-    const float a1 = a - __builtin_bit_cast(float, p.t[0] << 16);
-    const float b1 = b - __builtin_bit_cast(float, p.t[0] & 0xffff0000u);
-    p.t[1] = pack_bf16(a1, b1);
-    const float a2 = a1 - __builtin_bit_cast(float, p.t[1] << 16);
-    const float b2_ = b1 - __builtin_bit_cast(float, p.t[1] & 0xffff0000u);
-    p.t[2] = pack_bf16(a2, b2_);
-    return p;
-}
 
 // A multivector's matrix elements (REP).  k = 2: X = x0 + p sz + q sx + r e
 // with sz = diag(1, -1), sx = [[0, 1], [1, 0]], e = [[0, 1], [-1, 0]];

@@ -47,6 +47,7 @@ void check_act(const cliff::LaunchPlan& p);
 void check_linear(const cliff::LaunchPlan& p);
 void check_direct(const cliff::LaunchPlan& p);
 void check_conv_split(const cliff::LaunchPlan& p);
+void check_linear_split(const cliff::LaunchPlan& p);
 void check_generic(const cliff::LaunchPlan& p);
 
 }  // namespace hostcheck

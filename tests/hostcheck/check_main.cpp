@@ -94,6 +94,7 @@ static void on_launch(const cliff::LaunchPlan& p, void*)
     case cliff::LAUNCH_ACT: check_act(p); break;
     case cliff::LAUNCH_LINEAR_MFMA: check_linear(p); break;
     case cliff::LAUNCH_CONV_DIRECT: check_direct(p); break;
+    case cliff::LAUNCH_LINEAR_SPLIT: check_linear_split(p); break;
     case cliff::LAUNCH_CONV_SPLIT: check_conv_split(p); break;
     default: check_generic(p); break;
     }

@@ -55,3 +55,25 @@ def test_observer_without_the_kind():
     # a checker that cannot walk the kernel is not handed it
     res = HC.run([conv_line(2, (1, 1), 8, 64, 64, 128, 3, P.ALGO_AUTO)])[0].split()
     assert res[0] == "ok" and res[4] == "1", res
+
+
+def test_linear_layers():
+    # the split linear kernel, automatic and forced streamed: the GPU tests'
+    # layers and the benchmark's; smaller batches and other widths stay with
+    # the fp32 kernels
+    import test_linear_split_gpu as T
+    S = P.ALGO_MFMA_STREAM
+    cases = [(g, B, ci, co, gate, "8") for g, B, ci, co, gate, _ in T.CASES]
+    cases += [((1, 1), 1 << 20, 32, 32, None, "8"), ((1, 1), T.B0 - 1, 32, 32, None, None),
+              ((1,), 1 << 21, 32, 32, None, "4"), ((1, 1), 1 << 18, 24, 32, None, "1")]
+    lines, want = [], []
+    for g, B, ci, co, gate, kind in cases:
+        for algo in (P.ALGO_AUTO, S):
+            if kind == "1" and algo == S:
+                continue
+            lines.append(conv_line(len(g), g, B, ci, co, 1, 1, algo, gate))
+            want.append(kind or ("1" if algo == P.ALGO_AUTO else "4"))
+    out = HC.run(["kinds 8"] + lines)[1:]
+    for line, res, kind in zip(lines, out, want):
+        f = res.split()
+        assert f[0] == "ok" and f[4] == kind, (line, res, kind)
