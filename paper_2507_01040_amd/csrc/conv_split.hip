@@ -162,7 +162,7 @@ __global__ __launch_bounds__(64 * WCO * WPOS, 2) void conv_split_kernel(SplitArg
     constexpr int R = T.R(), S = T.S(), C = T.C(), CHI = T.chi();
     constexpr int NT = T.nt();
     constexpr int NC = NPT * S;  // column tiles of a wave
-    constexpr int NXMAX = DF > 0 ? DF : 4;  // strip rounds of a stage
+    constexpr int NXMAX = split_rounds(KD, DF);  // strip rounds of a stage
 
     extern __shared__ u4 smem4[];
     char* smem = reinterpret_cast<char*>(smem4);
@@ -618,7 +618,7 @@ cliff_status run(const ConvProblem& p, hipStream_t stream, int64_t* blocks)
     constexpr int per_round = T.waves() / T.nchi() * 64;
     const int64_t nx = (L + per_round - 1) / per_round;
     const int64_t xi = (nx + df - 1) / df;
-    if (L > LP || nx > (DF > 0 ? DF : 4) || xi > (DF > 0 ? 1 : 2)) return CLIFF_EUNSUPPORTED;
+    if (L > LP || nx > split_rounds(KD, DF) || xi > (DF > 0 ? 1 : 2)) return CLIFF_EUNSUPPORTED;
     const int64_t n_co_blk = (p.C_out + T.co_wg() - 1) / T.co_wg();
     const int64_t n_blk = (M + P - 1) / P * n_co_blk;
     const int64_t n_grp = (p.C_in + T.cpg() - 1) / T.cpg();
@@ -711,12 +711,20 @@ cliff_status launch_df(const ConvProblem& p, hipStream_t stream, double most_us)
     static constexpr Shape rep3[] = {shape<3, 8, DF, 1, 1, 4, 1, 148>(1.23, 2.27),
                                      shape<3, 8, DF, 1, 2, 2, 1, 84>(1.25, 2.32),
                                      shape<3, 8, DF, 1, 2, 4, 1, 288>(2.12, 4.17)};
+    // k = 1: 64 x 256, 64 x 128, 64 x 512, 32 x 512, 32 x 256
+    static constexpr Shape gen1[] = {
+        shape<1, 2, 0, 0, 2, 4, 2, 512>(1.70, 3.40), shape<1, 2, 0, 0, 2, 2, 2, 256>(1.08, 1.76),
+        shape<1, 2, 0, 0, 2, 4, 4, 724>(3.10, 6.20), shape<1, 2, 0, 0, 1, 8, 2, 724>(1.78, 3.56),
+        shape<1, 2, 0, 0, 1, 4, 2, 360>(1.10, 1.83)};
     // 32 x 128, 32 x 256
     static constexpr Shape gen3[] = {shape<3, 8, DF, 0, 1, 4, 1, 168>(1.48, 2.28),
                                      shape<3, 8, DF, 0, 1, 8, 1, 320>(2.10, 4.17)};
     const Shape* s;
     int n;
-    if (p.k == 2) {
+    if (p.k == 1) {
+        s = gen1;
+        n = 5;
+    } else if (p.k == 2) {
         const bool rep = split_rep2(p.sign) >= 0;
         s = rep ? rep2 : gen2;
         n = rep ? 4 : 5;
@@ -755,14 +763,15 @@ cliff_status launch_df(const ConvProblem& p, hipStream_t stream, double most_us)
 cliff_status launch_conv_split(const ConvProblem& p, hipStream_t stream)
 {
     if (launch_observer && launch_observer->last_kind < LAUNCH_CONV_SPLIT) return CLIFF_EUNSUPPORTED;
-    if (p.k < 2 || p.d_filter < 2) return CLIFF_EUNSUPPORTED;
+    if (p.d_filter < 2) return CLIFF_EUNSUPPORTED;
     // Taken where the estimate is below the time of the fp32 tiles at their
-    // best rate (146 TFLOP/s, 0.93 of the fp32 peak, on the largest layers);
-    // smaller layers, where that rate is out of reach for either, stay there.
+    // best rate (146 TFLOP/s, 0.93 of the fp32 peak, on the largest layers;
+    // 141 for k = 1); smaller layers, where that rate is out of reach for
+    // either, stay there.
     double useful = 2.0 * (double)p.B * p.C_out * p.C_in * p.nb * p.nb;
     for (int t = 0; t < p.k; ++t) useful *= (double)p.d_out * p.d_filter;
-    const double most_us = useful / 146e6;
-    return p.d_filter == 3 ? launch_df<3>(p, stream, most_us) : launch_df<0>(p, stream, most_us);
+    const double most_us = useful / (p.k == 1 ? 141e6 : 146e6);
+    return p.k > 1 && p.d_filter == 3 ? launch_df<3>(p, stream, most_us) : launch_df<0>(p, stream, most_us);
 }
 
 }  // namespace cliff

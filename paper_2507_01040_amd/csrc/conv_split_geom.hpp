@@ -78,6 +78,10 @@ struct SplitTile {
     __host__ __device__ constexpr int lds_bytes() const { return 2 * (a_bytes() + x_bytes()); }
 };
 
+// The most strip rounds of a stage: one for each of the DF tap columns where
+// their number is fixed, else what a lane keeps offsets for.
+__host__ __device__ constexpr int split_rounds(int KD, int DF) { return DF > 0 ? DF : KD == 1 ? 8 : 4; }
+
 // LDS byte offsets of the planes: term t (0 high, 1 middle, 2 low part),
 // matrix row r or column c, chunk g of 8 K slots.
 __host__ __device__ constexpr int split_a_plane(const SplitTile& T, int t, int r, int g)

@@ -50,7 +50,7 @@ void walk(const LaunchPlan& p, const SplitTile& T, const SplitArgs& a)
         return;
     }
     const int64_t n_grp = (a.C_in + T.cpg() - 1) / T.cpg();
-    if (a.nx > 4 || a.xi > 2 || (int64_t)a.xi * a.df < a.nx || a.n_step != n_grp * a.taps ||
+    if (a.nx > split_rounds(KD, 0) || a.xi > 2 || (int64_t)a.xi * a.df < a.nx || a.n_step != n_grp * a.taps ||
         a.nrt * a.df != a.taps || a.nrow * a.Do != a.M || (bb && bb->n < (int64_t)a.C_out * NB)) {
         fail("stage plan: nx %d xi %d n_step %d", a.nx, a.xi, a.n_step);
         return;
@@ -63,7 +63,7 @@ void walk(const LaunchPlan& p, const SplitTile& T, const SplitArgs& a)
         return;
     }
     const int64_t B = a.M / a.npos;
-    const bool sampled = a.n_blk > 256;
+    const bool sampled = a.n_blk > 64;
     if (sampled) current->grid_sampled = true;
     std::vector<uint8_t> seen;
     const bool count = (int64_t)a.n_blk * T.pos() * T.co_wg() < (1 << 26);

@@ -40,6 +40,11 @@ CASES = [
     ((1, 1, 1), (64, 7, 60, 10, 3), None, False, "1.2.4.1"),
     ((1, -1, 1), (8, 6, 20, 34, 3), None, True, "0.1.8.1"),
     ((0, 0, 1), (64, 7, 60, 10, 3), (SUM, (4, 1)), True, "0.1.4.1"),
+    ((-1,), (2000, 21, 62, 61, 17), (LIN, (1, 0)), True, "0.2.2.2"),
+    ((1,), (700, 32, 64, 260, 5), None, False, "0.2.4.2"),
+    ((-1,), (1024, 13, 64, 515, 9), (MEAN, (1,)), True, "0.2.4.4"),
+    ((-1,), (5800, 32, 30, 60, 17), (SUM, (0, 1)), True, "0.1.8.2"),
+    ((1,), (512, 93, 96, 200, 5), None, True, "0.1.4.2"),
 ]
 IDS = ["%s-%s" % ("".join(str(v) for v in g), "x".join(str(v) for v in s)) for g, s, _, _, _ in CASES]
 
@@ -78,7 +83,9 @@ def test_conv_split(case):
     assert np.isfinite(y).all()
     z = _run(g, x, f, b, act, P.ALGO_MFMA)
     assert not np.array_equal(y, z)  # not the fp32 kernels' result
-    sel = sorted({0, shape[0] - 1})
+    sel = sorted({0, 1, 2, shape[0] // 2, shape[0] - 2, shape[0] - 1} & set(range(shape[0])))
+    if len(g) > 1:
+        sel = sorted({0, shape[0] - 1})
     ref = oracle.conv_nd(x[sel], f, np.zeros((shape[2], 1 << len(g)), np.float32) if b is None else b, g)
     if act is not None:
         ref = oracle.act(ref, *act)
