@@ -29,6 +29,14 @@
 // converts them after the step's MFMAs and writes the parts to the other slot
 // and buffer; one barrier per step.
 //
+// 16 channels (CW).  An MFMA row tile holds 32 channels of one matrix row (or
+// output blade), or 16 channels of two: the lane that has (channel, position)
+// then finds the second one eight registers on.  Layers of up to 16 channels,
+// or of a last block of up to 16, ran half of their MFMAs on padding: k = 2,
+// B 8, C 16, d 258 230 -> 179 us in matrix form, 342 -> 193 us expanded (fp32
+// tiles: 303, 283); k = 3, B 8, C 16, d 34 966 -> 610 us (fp32 tiles: 1615).
+// The staging and the barrier of a step stay, so wider layers keep 32.
+//
 // Bound: the bf16 matrix cores at the clock their power allows.  A loop of
 // 32x32x16 MFMAs on random registers reaches 1793 TFLOP/s (2485 on zeros);
 // this kernel's MFMAs run at 1340 (k = 2, matrix form) to 1440 TFLOP/s (k = 3)
@@ -155,11 +163,11 @@ __device__ void plain_output(const SplitArgs& a, int m, int co, float (&v)[8])
     }
 }
 
-template <int KD, int NB, int DF, int REP, int WCO, int WPOS, int NPT, int LP>
+template <int KD, int NB, int DF, int REP, int WCO, int WPOS, int NPT, int LP, int CW>
 __global__ __launch_bounds__(64 * WCO * WPOS, 2) void conv_split_kernel(SplitArgs a)
 {
-    constexpr SplitTile T{KD, NB, REP, WCO, WPOS, NPT, LP};
-    constexpr int R = T.R(), S = T.S(), C = T.C(), CHI = T.chi();
+    constexpr SplitTile T{KD, NB, REP, WCO, WPOS, NPT, LP, CW};
+    constexpr int RPT = T.rpt(), R = T.R() / RPT, S = T.S(), C = T.C(), CHI = T.chi();
     constexpr int NT = T.nt();
     constexpr int NC = NPT * S;  // column tiles of a wave
     constexpr int NXMAX = split_rounds(KD, DF);  // strip rounds of a stage
@@ -390,7 +398,7 @@ __global__ __launch_bounds__(64 * WCO * WPOS, 2) void conv_split_kernel(SplitArg
     constexpr bool HOLD_A = R <= NC;
     constexpr int NH = HOLD_A ? R : NC, NS = HOLD_A ? NC : R;
     auto compute = [&](int slot, int off, auto load, auto convert) {
-        auto rd_a = [&](int r, int t) { return frag(fa0 + slot + split_a_plane(T, t, r, 0)); };
+        auto rd_a = [&](int r, int t) { return frag(fa0 + slot + split_a_plane(T, t, r * RPT, 0)); };
         auto rd_b = [&](int n, int t) {
             return frag(fb0[n / S] + off + split_x_plane(T, t, n % S, 0));
         };
@@ -542,18 +550,21 @@ __global__ __launch_bounds__(64 * WCO * WPOS, 2) void conv_split_kernel(SplitArg
                 reinterpret_cast<f4*>(yp)[h] = f4{v[4 * h], v[4 * h + 1], v[4 * h + 2], v[4 * h + 3]};
         }
     };
+    // element e of row r: with 16 channels to a row, odd rows are the row
+    // tile's upper half
+    auto el = [&](int r, int n, int e) { return acc[r / RPT][n][e + r % RPT * (CW / 2)]; };
     uint32_t bad[NPT];
 #pragma unroll
     for (int np = 0; np < NPT; ++np) {
         const int m = split_out_m(T, g, wave, lane, np);
         bad[np] = 0;
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
+        for (int e = 0; e < CW / 2; ++e) {
             const int co = split_out_co(T, g, wave, lane, e);
             float v[8];
             if constexpr (REP && NB == 4) {
-                const float M[4] = {acc[0][np * 2][e], acc[0][np * 2 + 1][e], acc[1][np * 2][e],
-                                    acc[1][np * 2 + 1][e]};
+                const float M[4] = {el(0, np * 2, e), el(0, np * 2 + 1, e), el(1, np * 2, e),
+                                    el(1, np * 2 + 1, e)};
                 from_matrix(M, a.rep, v);
             } else if constexpr (REP) {
                 float M[8];
@@ -563,11 +574,11 @@ __global__ __launch_bounds__(64 * WCO * WPOS, 2) void conv_split_kernel(SplitArg
                     for (int c = 0; c < 2; ++c)
 #pragma unroll
                         for (int ri = 0; ri < 2; ++ri)
-                            M[2 * (2 * r + c) + ri] = acc[2 * r + ri][np * 2 + c][e];
+                            M[2 * (2 * r + c) + ri] = el(2 * r + ri, np * 2 + c, e);
                 from_matrix3(M, v);
             } else {
 #pragma unroll
-                for (int i = 0; i < NB; ++i) v[blade_perm(NB, i)] = acc[i][np][e];
+                for (int i = 0; i < NB; ++i) v[blade_perm(NB, i)] = el(i, np, e);
             }
             if (m < g.m_end && co < a.C_out) {
                 float z = 0.f;
@@ -592,10 +603,10 @@ __global__ __launch_bounds__(64 * WCO * WPOS, 2) void conv_split_kernel(SplitArg
     }
 }
 
-template <int KD, int NB, int DF, int REP, int WCO, int WPOS, int NPT, int LP>
+template <int KD, int NB, int DF, int REP, int WCO, int WPOS, int NPT, int LP, int CW>
 cliff_status run(const ConvProblem& p, hipStream_t stream, int64_t* blocks)
 {
-    constexpr SplitTile T{KD, NB, REP, WCO, WPOS, NPT, LP};
+    constexpr SplitTile T{KD, NB, REP, WCO, WPOS, NPT, LP, CW};
     static_assert(T.lds_bytes() <= 160 * 1024, "LDS");
     const int64_t D = p.d_image, Do = p.d_out, df = p.d_filter, P = T.pos();
     int64_t npos = 1, img = 1, taps = 1;
@@ -669,11 +680,11 @@ cliff_status run(const ConvProblem& p, hipStream_t stream, int64_t* blocks)
                 "%lld workgroups of %d, %d LDS bytes\n",
                 KD, (int)df, REP ? "matrices" : "blades", T.co_wg(), (int)P, (long long)n_blk,
                 T.nt(), T.lds_bytes());
-    if (observe_launch(LAUNCH_CONV_SPLIT, {KD, NB, REP, WCO, WPOS, NPT, LP}, n_blk, T.nt(),
+    if (observe_launch(LAUNCH_CONV_SPLIT, {KD, NB, REP, WCO, WPOS, NPT, LP, CW}, n_blk, T.nt(),
                        T.lds_bytes(), &a))
         return CLIFF_OK;
     clear_hip_error();
-    hipLaunchKernelGGL((conv_split_kernel<KD, NB, DF, REP, WCO, WPOS, NPT, LP>), dim3((unsigned)n_blk),
+    hipLaunchKernelGGL((conv_split_kernel<KD, NB, DF, REP, WCO, WPOS, NPT, LP, CW>), dim3((unsigned)n_blk),
                        dim3(T.nt()), (size_t)T.lds_bytes(), stream, a);
     return hipGetLastError() == hipSuccess ? CLIFF_OK : CLIFF_EDEVICE;
 }
@@ -684,33 +695,37 @@ cliff_status run(const ConvProblem& p, hipStream_t stream, int64_t* blocks)
 // fill a CU alone).
 struct Shape {
     cliff_status (*run)(const ConvProblem&, hipStream_t, int64_t*);
-    int cpg;
+    int cpg, cw;
     double t1, t2;
 };
-template <int KD, int NB, int DF, int REP, int WCO, int WPOS, int NPT, int LP>
+template <int KD, int NB, int DF, int REP, int WCO, int WPOS, int NPT, int LP, int CW = 32>
 constexpr Shape shape(double t1, double t2)
 {
-    return Shape{run<KD, NB, DF, REP, WCO, WPOS, NPT, LP>,
-                 SplitTile{KD, NB, REP, WCO, WPOS, NPT, LP}.cpg(), t1, t2};
+    return Shape{run<KD, NB, DF, REP, WCO, WPOS, NPT, LP, CW>,
+                 SplitTile{KD, NB, REP, WCO, WPOS, NPT, LP, CW}.cpg(), CW, t1, t2};
 }
 
 template <int DF>
 cliff_status launch_df(const ConvProblem& p, hipStream_t stream, double most_us)
 {
     // 64 x 256, 64 x 128, 32 x 256, 32 x 128 (channels x positions; 64 x 64
-    // measured 1.20, 1.70: never ahead of 32 x 128)
+    // measured 1.20, 1.70: never ahead of 32 x 128), 16 x 256, 16 x 128
     static constexpr Shape rep2[] = {
         shape<2, 4, DF, 1, 2, 4, 2, 320>(2.43, 4.70), shape<2, 4, DF, 1, 2, 2, 2, 148>(1.55, 2.60),
-        shape<2, 4, DF, 1, 1, 8, 1, 320>(1.47, 2.79), shape<2, 4, DF, 1, 1, 4, 1, 148>(1.18, 1.61)};
-    // ... and 64 x 64
+        shape<2, 4, DF, 1, 1, 8, 1, 320>(1.47, 2.79), shape<2, 4, DF, 1, 1, 4, 1, 148>(1.18, 1.61),
+        shape<2, 4, DF, 1, 1, 8, 1, 320, 16>(0.98, 1.99),
+        shape<2, 4, DF, 1, 1, 4, 1, 148, 16>(0.74, 1.02)};
+    // ... and 64 x 64, 16 x 256 (16 x 128: 62 against 59, 217 against 193 us)
     static constexpr Shape gen2[] = {
         shape<2, 4, DF, 0, 2, 4, 2, 320>(2.13, 4.18), shape<2, 4, DF, 0, 2, 2, 2, 168>(1.19, 2.23),
         shape<2, 4, DF, 0, 1, 8, 1, 320>(1.12, 2.20), shape<2, 4, DF, 0, 1, 4, 1, 168>(0.76, 1.27),
-        shape<2, 4, DF, 0, 2, 2, 1, 100>(0.75, 1.36)};
-    // 32 x 128, 64 x 64, 64 x 128
+        shape<2, 4, DF, 0, 2, 2, 1, 100>(0.75, 1.36),
+        shape<2, 4, DF, 0, 1, 8, 1, 320, 16>(0.75, 1.25)};
+    // 32 x 128, 64 x 64, 64 x 128, 16 x 128
     static constexpr Shape rep3[] = {shape<3, 8, DF, 1, 1, 4, 1, 148>(1.23, 2.27),
                                      shape<3, 8, DF, 1, 2, 2, 1, 84>(1.25, 2.32),
-                                     shape<3, 8, DF, 1, 2, 4, 1, 288>(2.12, 4.17)};
+                                     shape<3, 8, DF, 1, 2, 4, 1, 288>(2.12, 4.17),
+                                     shape<3, 8, DF, 1, 1, 4, 1, 148, 16>(1.05, 1.41)};
     // k = 1: 64 x 256, 64 x 128, 64 x 512, 32 x 512, 32 x 256
     static constexpr Shape gen1[] = {
         shape<1, 2, 0, 0, 2, 4, 2, 512>(1.70, 3.40), shape<1, 2, 0, 0, 2, 2, 2, 256>(1.08, 1.76),
@@ -727,10 +742,10 @@ cliff_status launch_df(const ConvProblem& p, hipStream_t stream, double most_us)
     } else if (p.k == 2) {
         const bool rep = split_rep2(p.sign) >= 0;
         s = rep ? rep2 : gen2;
-        n = rep ? 4 : 5;
+        n = 6;
     } else if (split_rep3(p.sign)) {
         s = rep3;
-        n = 3;
+        n = 4;
     } else {
         s = gen3;
         n = 2;
@@ -745,6 +760,9 @@ cliff_status launch_df(const ConvProblem& p, hipStream_t stream, double most_us)
     double best_us = most_us;
     for (int i = 0; i < n; ++i) {
         int64_t blocks = 0;
+        // 16 channels only where blocks of 32 leave half of the last one empty
+        // (others were not measured)
+        if (s[i].cw == 16 && (p.C_out - 1) % 32 >= 16) continue;
         if (s[i].run(p, stream, &blocks) != CLIFF_OK) continue;
         const int64_t w = (blocks + cus - 1) / cus;
         const double steps = (double)((p.C_in + s[i].cpg - 1) / s[i].cpg) * std::pow(df, p.k);

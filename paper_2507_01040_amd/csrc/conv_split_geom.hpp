@@ -49,19 +49,20 @@ inline bool split_rep3(const SignMasks& s)
 // The compile-time shape of one kernel instantiation.  KD spatial dimensions,
 // NB blades; REP: 2x2 matrices stand for the multivectors (else the expanded
 // kernel); WCO x WPOS waves, each 32 output channels by 32 * NPT positions;
-// LP input positions staged per K group.
-//   R   rows of 32 output channels per wave (matrix rows, real and imaginary
-//       parts apart, or output blades)
+// LP input positions staged per K group; CW output channels a wave, 32 or 16.
+//   R   rows of CW output channels per wave (matrix rows, real and imaginary
+//       parts apart, or output blades); 32 / CW of them fill an MFMA row tile
 //   C   inner index of one input channel (K slots)
 //   S   columns of one position
 struct SplitTile {
-    int KD, NB, REP, WCO, WPOS, NPT, LP;
+    int KD, NB, REP, WCO, WPOS, NPT, LP, CW = 32;
     __host__ __device__ constexpr int R() const { return REP ? NB / 2 : NB; }
+    __host__ __device__ constexpr int rpt() const { return 32 / CW; }  // rows of a row tile
     __host__ __device__ constexpr int C() const { return REP ? NB / 2 : NB; }
     __host__ __device__ constexpr int S() const { return REP ? 2 : 1; }
     __host__ __device__ constexpr int waves() const { return WCO * WPOS; }
     __host__ __device__ constexpr int nt() const { return 64 * waves(); }
-    __host__ __device__ constexpr int co_wg() const { return 32 * WCO; }
+    __host__ __device__ constexpr int co_wg() const { return CW * WCO; }
     __host__ __device__ constexpr int pos() const { return 32 * NPT * WPOS; }
     // input channels of one K group (16 slots), of one 8-slot chunk, and of
     // one lane's conversion item (8 slots at most, 8 filter floats at most)
@@ -202,9 +203,12 @@ __host__ __device__ inline int split_a_lds(const SplitTile& T, int e)
 }
 
 // MFMA fragment reads of a lane (add the plane of term and row or column).
+// MFMA row lane % 32 of a row tile is output channel lane % CW of the wave, in
+// row (lane % 32) / CW of the tile's.
 __host__ __device__ inline int split_a_frag(const SplitTile& T, int wave, int lane)
 {
-    return (lane >> 5) * T.a_plane() + ((wave % T.WCO) * 32 + (lane & 31)) * 16;
+    return ((lane & 31) / T.CW * 2 + (lane >> 5)) * T.a_plane() +
+           ((wave % T.WCO) * T.CW + lane % T.CW) * 16;
 }
 __host__ __device__ inline int split_b_frag(const SplitTile& T, const SplitArgs& a,
                                             const SplitBlock& g, int wave, int lane, int np)
@@ -213,12 +217,12 @@ __host__ __device__ inline int split_b_frag(const SplitTile& T, const SplitArgs&
     return (lane >> 5) * T.x_plane() + split_run(a, g, m) * 16;
 }
 
-// Output channel of accumulator register r (0..15) and position of column
-// tile np of a lane.
+// Output channel of accumulator register r (0..CW / 2 - 1, of a row tile's first
+// row) and position of column tile np of a lane.
 __host__ __device__ inline int split_out_co(const SplitTile& T, const SplitBlock& g, int wave,
                                             int lane, int r)
 {
-    return g.co0 + (wave % T.WCO) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+    return g.co0 + (wave % T.WCO) * T.CW + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
 }
 __host__ __device__ inline int split_out_m(const SplitTile& T, const SplitBlock& g, int wave,
                                            int lane, int np)

@@ -100,7 +100,7 @@ void walk(const LaunchPlan& p, const SplitTile& T, const SplitArgs& a)
             for (int wave = 0; wave < T.waves(); ++wave)
                 for (int lane = 0; lane < 64; ++lane)
                     for (int np = 0; np < T.NPT; ++np)
-                        for (int r = 0; r < 16; ++r) {
+                        for (int r = 0; r < T.CW / 2; ++r) {
                             const int m = split_out_m(T, g, wave, lane, np);
                             const int co = split_out_co(T, g, wave, lane, r);
                             if (m >= g.m_end || co >= a.C_out) continue;
@@ -202,10 +202,13 @@ void walk(const LaunchPlan& p, const SplitTile& T, const SplitArgs& a)
             for (int wave = 0; wave < T.waves(); ++wave)
                 for (int lane = 0; lane < 64; ++lane)
                     for (int h = 0; h < T.cpc(); ++h) {
-                        const int at = split_a_frag(T, wave, lane) + h * SLOT;
+                        // row (lane % 32) / CW of the row tile: its pair of planes
+                        const int at = split_a_frag(T, wave, lane) + h * SLOT -
+                                       (split_a_plane(T, 0, (lane & 31) / T.CW, 0) -
+                                        split_a_plane(T, 0, 0, 0));
                         const int ci = ci0 + (lane >> 5) * T.cpc() + h;
-                        // MFMA row lane % 32 holds output channel row % 32 of the wave
-                        const int co = g.co0 + (wave % T.WCO) * 32 + (lane & 31);
+                        // MFMA row lane % 32 holds output channel row % CW of the wave
+                        const int co = g.co0 + (wave % T.WCO) * T.CW + (lane & 31) % T.CW;
                         if (at < 0 || at + SLOT > 2 * T.a_plane()) {
                             fail("filter fragment at %d", at);
                             return;
@@ -241,7 +244,8 @@ void walk(const LaunchPlan& p, const SplitTile& T, const SplitArgs& a)
 void check_conv_split(const LaunchPlan& p)
 {
     const SplitArgs& a = *static_cast<const SplitArgs*>(p.args);
-    const SplitTile T{p.tpl[0], p.tpl[1], p.tpl[2], p.tpl[3], p.tpl[4], p.tpl[5], p.tpl[6]};
+    const SplitTile T{p.tpl[0], p.tpl[1], p.tpl[2], p.tpl[3], p.tpl[4], p.tpl[5], p.tpl[6],
+                      p.tpl[7]};
     if (T.KD == 1) walk<1>(p, T, a);
     if (T.KD == 2) walk<2>(p, T, a);
     if (T.KD == 3) walk<3>(p, T, a);

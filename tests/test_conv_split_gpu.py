@@ -22,7 +22,7 @@ pytestmark = pytest.mark.gpu
 
 LIN, SUM, MEAN = P.AGG_LINEAR, P.AGG_SUM, P.AGG_MEAN
 # (g, (B, C_in, C_out, d_image, d_filter), gate (mode, blades) or None, bias,
-#  tile REP.WCO.WPOS.NPT)
+#  tile REP.WCO.WPOS.NPT, with .16 where a wave has 16 channels instead of 32)
 CASES = [
     ((1, 1), (4, 9, 62, 130, 3), None, True, "1.2.4.2"),
     ((1, 1), (1, 8, 64, 300, 3), (LIN, (0, 1, 2, 3)), True, "1.2.2.2"),
@@ -45,6 +45,13 @@ CASES = [
     ((-1,), (1024, 13, 64, 515, 9), (MEAN, (1,)), True, "0.2.4.4"),
     ((-1,), (5800, 32, 30, 60, 17), (SUM, (0, 1)), True, "0.1.8.2"),
     ((1,), (512, 93, 96, 200, 5), None, True, "0.1.4.2"),
+    ((1, 1), (5, 13, 16, 258, 3), (LIN, (0, 1, 2, 3)), True, "1.1.8.1.16"),
+    ((-1, 1), (3, 24, 11, 131, 5), None, True, "1.1.8.1.16"),
+    ((1, -1), (9, 64, 16, 67, 3), (SUM, (3, 1)), False, "1.1.8.1.16"),
+    ((-1, 0), (5, 13, 15, 258, 3), (MEAN, (0, 2)), True, "0.1.8.1.16"),
+    ((1, 1), (4, 8, 16, 300, 3), None, True, "1.1.4.1.16"),
+    ((1, 1, 1), (5, 7, 16, 34, 3), (LIN, (7, 0, 3)), True, "1.1.4.1.16"),
+    ((1, 1, 1), (5, 16, 13, 34, 2), None, False, "1.1.4.1.16"),
 ]
 IDS = ["%s-%s" % ("".join(str(v) for v in g), "x".join(str(v) for v in s)) for g, s, _, _, _ in CASES]
 
@@ -96,13 +103,15 @@ def test_conv_split(case):
     assert e <= 3 * ez
 
 
-@pytest.mark.parametrize("g", [(1, 1), (-1, 0), (1, 1, 1), (1, -1, 1)], ids=str)
-def test_conv_split_non_finite(g):
+@pytest.mark.parametrize("g,shape", [
+    ((1, 1), (1, 8, 64, 300, 3)), ((-1, 0), (1, 8, 64, 300, 3)), ((1, 1, 1), (2, 16, 32, 26, 3)),
+    ((1, -1, 1), (2, 16, 32, 26, 3)), ((1, 1), (4, 8, 16, 300, 3)), ((-1, 0), (4, 8, 16, 300, 3)),
+    ((1, 1, 1), (4, 16, 16, 34, 3))], ids=str)
+def test_conv_split_non_finite(g, shape):
     # infinities, NaN, the largest floats and products past them: outputs that
     # bf16 parts or sums of matrix elements cannot hold are those of the
     # vector kernel, the others are untouched
     k = len(g)
-    shape = (1, 8, 64, 300, 3) if k == 2 else (2, 16, 32, 26, 3)
     x, f, b, _ = _inputs(g, shape, None, True, 77)
     big = np.float32(3.3e38)
     x[(0, 3) + (4,) * k] = np.inf

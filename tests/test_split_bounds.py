@@ -27,7 +27,8 @@ def test_parity_cases():
     for res, (g, shape, _, _, tile) in zip(_run(lines), T.CASES):
         f = res.split()
         assert f[0] == "ok" and f[4] == "7", (g, shape, res)
-        assert ".".join(f[5].split(".")[2:6]) == tile, (g, shape, res)
+        t = f[5].split(".")
+        assert ".".join(t[2:6] + (["16"] if t[7] == "16" else [])) == tile, (g, shape, res)
 
 
 def test_benchmark_layers_and_sizes():
