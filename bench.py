@@ -10,7 +10,8 @@ Prints one JSON line.  ``value`` is useful GFLOP/s of the headline workload
 2 B C_out C_in N_B^2 d_filter^k d_out^k per convolution.  ``roofline`` is the
 dominant kernel's achieved TFLOP/s (useful FLOPs per launch / its average
 duration from HIP events on the launch stream) against the fp32 matrix-core
-peak.  ``cpu_baseline`` times the fp64 CPU oracle on a bounded sample of the
+peak; above 1 where the layer runs on the bf16 matrix cores with every fp32
+operand as three bf16 parts.  ``cpu_baseline`` times the fp64 CPU oracle on a bounded sample of the
 same workload on this host.  ``workloads`` reports the other workloads the
 same way (3D single conv; 2D/3D blocks with the fused-activation overhead),
 each with the oracle timed beside it (in full, or the 3D block's first batch
@@ -39,7 +40,10 @@ KERNEL_SOURCES = ["paper_2507_01040_amd/csrc/conv_mfma.hip",
                   "paper_2507_01040_amd/csrc/conv_mfma_geom.hpp",
                   "paper_2507_01040_amd/build.py",
                   "paper_2507_01040_amd/csrc/common.hpp",
-                  "paper_2507_01040_amd/csrc/epilogue.hpp"]
+                  "paper_2507_01040_amd/csrc/epilogue.hpp",
+                  "paper_2507_01040_amd/csrc/conv_split.hip",
+                  "paper_2507_01040_amd/csrc/conv_split_geom.hpp",
+                  "paper_2507_01040_amd/csrc/split.hpp"]
 
 
 def kernel_source_hash() -> str:
@@ -492,7 +496,7 @@ def main():
                      "peak": PEAK_FP32_MFMA_TFLOPS, "unit": "TFLOP/s",
                      "frac": round(achieved / PEAK_FP32_MFMA_TFLOPS, 4),
                      "traffic": _traffic(args.workload),
-                     "kernel": "conv_mfma_kernel (layer %d)" % dom,
+                     "kernel": "convolution, automatic choice (layer %d)" % dom,
                      "kernel_ms": dom_ms,
                      "kernel_source_hash": kernel_source_hash()},
         "workload_detail": head,
