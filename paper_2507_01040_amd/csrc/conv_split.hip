@@ -7,21 +7,18 @@
 // nearest: v = h + m + l to the last bit.  The products h h, h m, m h, m m,
 // h l, l h are kept; those left out are below 2^-24 of the operands' product.
 //
-// Matrix form (REP).  Where the algebra is that of the 2 x 2 real (k = 2,
-// g = (1, 1), (1, -1), (-1, 1)) or complex matrices (k = 3, g = (1, 1, 1)),
-// filters and inputs are taken into matrix elements while they are staged
-// (one add per element) and the product of two multivectors is a matrix
-// product: N_B^2 / 2 real multiply-adds instead of N_B^2.  Row r of the
-// filter's matrix gives 32 MFMA rows (32 output channels), column c of the
-// input's 32 MFMA columns (32 positions), and the epilogue, where one lane
-// holds all elements of a (channel, position), returns to blades.  Other
-// signatures run the expanded kernel: row i is output blade i, and the K slots
-// of an input channel are its blades j with filter blade i ^ j and the table's
-// sign.
+// Row i of an MFMA tile's rows is output blade i, and the K slots of an input
+// channel are its blades j with filter blade i ^ j and the table's sign, so
+// every product of two blades is taken by itself and a blade's sum never meets
+// another blade's.  For g = (1, 1), (1, -1), (-1, 1) and (1, 1, 1) the products
+// of 2 x 2 matrices would be half as many (k = 2, C 64, d 128 342 us), but their
+// elements are sums of blades, rounded in fp32: beside a blade 1e4 times as
+// large a blade's output kept two digits.  Any scheme of fewer products adds
+// blades, and no more parts help the accumulators that hold the sums.
 //
 // Work decomposition.  P consecutive flattened output positions by CO_WG
 // output channels per workgroup.  The K loop runs over steps: one group of 16
-// K slots (16 / C input channels) of one filter tap.  The three parts of the
+// K slots (16 / N_B input channels) of one filter tap.  The three parts of the
 // step's filters lie in an LDS ring of two slots, those of the input in two
 // buffers, one per stage (K group and row of filter taps: the taps of a row
 // read the same run of positions at a shift).  During a step each lane loads
@@ -29,29 +26,29 @@
 // converts them after the step's MFMAs and writes the parts to the other slot
 // and buffer; one barrier per step.
 //
-// 16 channels (CW).  An MFMA row tile holds 32 channels of one matrix row (or
-// output blade), or 16 channels of two: the lane that has (channel, position)
-// then finds the second one eight registers on.  Layers of up to 16 channels,
-// or of a last block of up to 16, ran half of their MFMAs on padding: k = 2,
-// B 8, C 16, d 258 230 -> 179 us in matrix form, 342 -> 193 us expanded (fp32
-// tiles: 303, 283); k = 3, B 8, C 16, d 34 966 -> 610 us (fp32 tiles: 1615).
-// The staging and the barrier of a step stay, so wider layers keep 32.
+// 16 channels (CW).  An MFMA row tile holds 32 channels of one output blade, or
+// 16 channels of two: the lane that has (channel, position) then finds the
+// second one eight registers on.  k = 2 layers of up to 16 channels, or of a
+// last block of up to 16, ran half of their MFMAs on padding: B 8, C 16, d 258
+// 342 -> 193 us (fp32 tiles: 289).  The staging and the barrier of a step stay,
+// so wider layers keep 32.
 //
 // Bound: the bf16 matrix cores at the clock their power allows.  A loop of
 // 32x32x16 MFMAs on random registers reaches 1793 TFLOP/s (2485 on zeros);
-// this kernel's MFMAs run at 1340 (k = 2, matrix form) to 1440 TFLOP/s (k = 3)
-// of it: without the staging (loads, conversions, LDS writes; a timing copy) a
-// step takes 10-14 % less, the rest is the barrier and the first fragments'
-// reads.  Measured against the fp32 tiles (start -> this kernel): k = 2, B 8,
-// C 64, d 128, 3x3 1077 -> 342 us; k = 3, B 8, C 32, d 32 5404 -> 1641 us;
-// block B 8, C 64, d 36 55.9 -> 16.4 ms; expanded kernel, g = (-1, -1), C 64,
-// d 128 1080 -> 594 us.  The error against 64 bits falls from 8.6e-7 to 5.2e-7
-// (2-norm, 2304 products), as 16 products go into one rounding.
-// Tried: 16x16x32 MFMAs with two products of parts in one (2055 TFLOP/s on
-// registers, but 28 instead of 18 KB of LDS reads a step and spills: 360 -> 428
-// us at k = 2), a third filter slot with fragments read ahead of the barrier
-// (335 -> 349 us), loads right after the conversions instead of at the start
-// of a step (360 -> 397 us), all taps of a row loaded at once (360 -> 369 us).
+// this kernel's MFMAs run at 1290 (k = 3, C 32, d 32) to 1500 TFLOP/s (k = 2,
+// C 64, d 128; k = 3, C 64, d 36); the rest is staging, the barrier and the
+// first fragments' reads.  Measured against the fp32 tiles: k = 2, B 8, C 64,
+// d 128, 3x3 1078 -> 601 us; k = 3, B 8, C 32, d 32 5426 -> 3550 us; C 64, d 36
+// 30.9 -> 17.8 ms; k = 1, B 4096, C 64, d 60, 17 taps 712 -> 510 us.  The error
+// against 64 bits falls from 8.6e-7 to 5.2e-7 (2-norm, 2304 products), as 16
+// products go into one rounding; where most products are zero (filters of one
+// blade) it is up to twice the fp32 tiles', six roundings to their four.
+// Tried on the 2 x 2 matrix form: 16x16x32 MFMAs with two products of parts in
+// one (2055 TFLOP/s on registers, but 28 instead of 18 KB of LDS reads a step
+// and spills: 360 -> 428 us at k = 2), a third filter slot with fragments read
+// ahead of the barrier (335 -> 349 us), loads right after the conversions
+// instead of at the start of a step (360 -> 397 us), all taps of a row loaded at
+// once (360 -> 369 us).
 //
 // Values that bf16 arithmetic cannot carry (infinities, sums past the largest
 // float) come out non-finite; such outputs are computed again, by the lane
@@ -78,54 +75,6 @@ typedef float f16 __attribute__((ext_vector_type(16)));
 typedef __bf16 b8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u4 __attribute__((ext_vector_type(4)));
-
-// A multivector's matrix elements (REP).  k = 2: X = x0 + p sz + q sx + r e
-// with sz = diag(1, -1), sx = [[0, 1], [1, 0]], e = [[0, 1], [-1, 0]];
-// rep 0: g = (1, 1), (p, q, r) = (x1, x2, x12); rep 1: g = (1, -1), (x1, x12,
-// x2); rep 2: g = (-1, 1), (x2, -x12, x1).  M[row][column].
-__device__ inline void to_matrix(const float (&x)[4], int rep, float (&M)[4])
-{
-    const float p = rep == 2 ? x[2] : x[1];
-    const float r = rep == 0 ? x[3] : rep == 1 ? x[2] : x[1];
-    float q = rep == 0 ? x[2] : x[3];
-    q = rep == 2 ? -q : q;
-    M[0] = x[0] + p;
-    M[1] = q + r;
-    M[2] = q - r;
-    M[3] = x[0] - p;
-}
-__device__ inline void from_matrix(const float (&M)[4], int rep, float (&v)[8])
-{
-    const float p = 0.5f * (M[0] - M[3]), q = 0.5f * (M[1] + M[2]), r = 0.5f * (M[1] - M[2]);
-    v[0] = 0.5f * (M[0] + M[3]);
-    v[1] = rep == 2 ? r : p;
-    v[2] = rep == 0 ? q : rep == 1 ? r : p;
-    v[3] = rep == 0 ? r : rep == 1 ? q : -q;
-}
-// k = 3, g = (1, 1, 1): the Pauli matrices for e1, e2, e3.  M[2 * (2 * row +
-// column) + (0 real, 1 imaginary)].
-__device__ inline void to_matrix3(const float (&x)[8], float (&M)[8])
-{
-    M[0] = x[0] + x[3];
-    M[1] = x[7] + x[4];
-    M[2] = x[1] - x[5];
-    M[3] = x[6] - x[2];
-    M[4] = x[1] + x[5];
-    M[5] = x[6] + x[2];
-    M[6] = x[0] - x[3];
-    M[7] = x[7] - x[4];
-}
-__device__ inline void from_matrix3(const float (&M)[8], float (&v)[8])
-{
-    v[0] = 0.5f * (M[0] + M[6]);
-    v[3] = 0.5f * (M[0] - M[6]);
-    v[7] = 0.5f * (M[1] + M[7]);
-    v[4] = 0.5f * (M[1] - M[7]);
-    v[1] = 0.5f * (M[4] + M[2]);
-    v[5] = 0.5f * (M[4] - M[2]);
-    v[6] = 0.5f * (M[5] + M[3]);
-    v[2] = 0.5f * (M[5] - M[3]);
-}
 
 // One output multivector as plain fp32 sums.
 template <int KD, int NB>
@@ -163,13 +112,12 @@ __device__ void plain_output(const SplitArgs& a, int m, int co, float (&v)[8])
     }
 }
 
-template <int KD, int NB, int DF, int REP, int WCO, int WPOS, int NPT, int LP, int CW>
+template <int KD, int NB, int DF, int WCO, int WPOS, int NPT, int LP, int CW>
 __global__ __launch_bounds__(64 * WCO * WPOS, 2) void conv_split_kernel(SplitArgs a)
 {
-    constexpr SplitTile T{KD, NB, REP, WCO, WPOS, NPT, LP, CW};
-    constexpr int RPT = T.rpt(), R = T.R() / RPT, S = T.S(), C = T.C(), CHI = T.chi();
+    constexpr SplitTile T{KD, NB, WCO, WPOS, NPT, LP, CW};
+    constexpr int RPT = T.rpt(), R = NB / RPT, CHI = T.chi();
     constexpr int NT = T.nt();
-    constexpr int NC = NPT * S;  // column tiles of a wave
     constexpr int NXMAX = split_rounds(KD, DF);  // strip rounds of a stage
 
     extern __shared__ u4 smem4[];
@@ -237,8 +185,8 @@ __global__ __launch_bounds__(64 * WCO * WPOS, 2) void conv_split_kernel(SplitArg
 #pragma unroll
         for (int c = 0; c < CHI; ++c) load_mv(wdesc, agoff + (off + c * a_chan), 0, v[c]);
     };
-    auto write_slots = [&](char* p, const uint32_t* d) {  // CHI * C slots of one plane
-        if constexpr (CHI * C == 4)
+    auto write_slots = [&](char* p, const uint32_t* d) {  // CHI * NB slots of one plane
+        if constexpr (CHI * NB == 4)
             *reinterpret_cast<u2*>(p) = u2{d[0], d[1]};
         else
             *reinterpret_cast<u4*>(p) = u4{d[0], d[1], d[2], d[3]};
@@ -246,62 +194,29 @@ __global__ __launch_bounds__(64 * WCO * WPOS, 2) void conv_split_kernel(SplitArg
     auto store_a = [&](int slot, const float (&ra)[CHI][NB]) {
         if (!a_on) return;
         char* const p = aw + slot;
-        if constexpr (REP && NB == 4) {
-            float M[CHI][4];
+        // K slots in bitmask order; row i takes blade i ^ j for slot j
+        constexpr int NP = NB / 2;
+        Parts s[CHI][NP];
 #pragma unroll
-            for (int c = 0; c < CHI; ++c) to_matrix(ra[c], a.rep, M[c]);
+        for (int c = 0; c < CHI; ++c)
 #pragma unroll
-            for (int r = 0; r < 2; ++r) {
-                const Parts s0 = split2(M[0][2 * r], M[0][2 * r + 1]);
-                const Parts s1 = split2(M[1][2 * r], M[1][2 * r + 1]);
+            for (int h = 0; h < NP; ++h)
+                s[c][h] = split2(ra[c][blade_perm(NB, 2 * h)], ra[c][blade_perm(NB, 2 * h + 1)]);
 #pragma unroll
-                for (int t = 0; t < 3; ++t) {
-                    const uint32_t d[2] = {s0.t[t], s1.t[t]};
-                    write_slots(p + split_a_plane(T, t, r, 0), d);
-                }
+        for (int t = 0; t < 3; ++t)
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                uint32_t d[CHI * NP];
+#pragma unroll
+                for (int c = 0; c < CHI; ++c)
+#pragma unroll
+                    for (int h = 0; h < NP; ++h) {
+                        uint32_t v = s[c][h ^ (i >> 1)].t[t];
+                        if (i & 1) v = __builtin_amdgcn_alignbit(v, v, 16);
+                        d[c * NP + h] = (v ^ a.sx[i * NP + h]) & a.sz[i * NP + h];
+                    }
+                write_slots(p + split_a_plane(T, t, i, 0), d);
             }
-        } else if constexpr (REP) {
-            float M[8];
-            to_matrix3(ra[0], M);
-#pragma unroll
-            for (int r = 0; r < 2; ++r) {
-                const Parts s0 = split2(M[4 * r], M[4 * r + 1]);
-                const Parts s1 = split2(M[4 * r + 2], M[4 * r + 3]);
-#pragma unroll
-                for (int t = 0; t < 3; ++t) {
-                    // (re, -im) for the real row, (im, re) for the imaginary one
-                    const uint32_t re[2] = {s0.t[t] ^ 0x80000000u, s1.t[t] ^ 0x80000000u};
-                    const uint32_t im[2] = {__builtin_amdgcn_alignbit(s0.t[t], s0.t[t], 16),
-                                            __builtin_amdgcn_alignbit(s1.t[t], s1.t[t], 16)};
-                    write_slots(p + split_a_plane(T, t, 2 * r, 0), re);
-                    write_slots(p + split_a_plane(T, t, 2 * r + 1, 0), im);
-                }
-            }
-        } else {
-            // K slots in bitmask order; row i takes blade i ^ j for slot j
-            constexpr int NP = NB / 2;
-            Parts s[CHI][NP];
-#pragma unroll
-            for (int c = 0; c < CHI; ++c)
-#pragma unroll
-                for (int h = 0; h < NP; ++h)
-                    s[c][h] = split2(ra[c][blade_perm(NB, 2 * h)], ra[c][blade_perm(NB, 2 * h + 1)]);
-#pragma unroll
-            for (int t = 0; t < 3; ++t)
-#pragma unroll
-                for (int i = 0; i < NB; ++i) {
-                    uint32_t d[CHI * NP];
-#pragma unroll
-                    for (int c = 0; c < CHI; ++c)
-#pragma unroll
-                        for (int h = 0; h < NP; ++h) {
-                            uint32_t v = s[c][h ^ (i >> 1)].t[t];
-                            if (i & 1) v = __builtin_amdgcn_alignbit(v, v, 16);
-                            d[c * NP + h] = (v ^ a.sx[i * NP + h]) & a.sz[i * NP + h];
-                        }
-                    write_slots(p + split_a_plane(T, t, i, 0), d);
-                }
-        }
     };
     // raw input of one strip of a stage (tap column 0); channels past C_in
     // have a descriptor of size zero, which reads zeros
@@ -327,57 +242,28 @@ __global__ __launch_bounds__(64 * WCO * WPOS, 2) void conv_split_kernel(SplitArg
     auto store_x = [&](int buf, int lds, bool on, const float (&v)[CHI][NB]) {
         if (!on) return;
         char* const p = lx + buf + lds;
-        if constexpr (REP && NB == 4) {
-            float M[CHI][4];
+        constexpr int NP = NB / 2;
+        Parts s[CHI * NP];
 #pragma unroll
-            for (int c = 0; c < CHI; ++c) to_matrix(v[c], a.rep, M[c]);
+        for (int c = 0; c < CHI; ++c)
 #pragma unroll
-            for (int col = 0; col < 2; ++col) {
-                const Parts s0 = split2(M[0][col], M[0][2 + col]);
-                const Parts s1 = split2(M[1][col], M[1][2 + col]);
+            for (int h = 0; h < NP; ++h)
+                s[c * NP + h] =
+                    split2(v[c][blade_perm(NB, 2 * h)], v[c][blade_perm(NB, 2 * h + 1)]);
 #pragma unroll
-                for (int t3 = 0; t3 < 3; ++t3) {
-                    const uint32_t d[2] = {s0.t[t3], s1.t[t3]};
-                    write_slots(p + split_x_plane(T, t3, col, 0), d);
-                }
-            }
-        } else if constexpr (REP) {
-            float M[8];
-            to_matrix3(v[0], M);
+        for (int t3 = 0; t3 < 3; ++t3) {
+            uint32_t d[CHI * NP];
 #pragma unroll
-            for (int col = 0; col < 2; ++col) {
-                const Parts s0 = split2(M[2 * col], M[2 * col + 1]);
-                const Parts s1 = split2(M[4 + 2 * col], M[5 + 2 * col]);
-#pragma unroll
-                for (int t3 = 0; t3 < 3; ++t3) {
-                    const uint32_t d[2] = {s0.t[t3], s1.t[t3]};
-                    write_slots(p + split_x_plane(T, t3, col, 0), d);
-                }
-            }
-        } else {
-            constexpr int NP = NB / 2;
-            Parts s[CHI * NP];
-#pragma unroll
-            for (int c = 0; c < CHI; ++c)
-#pragma unroll
-                for (int h = 0; h < NP; ++h)
-                    s[c * NP + h] =
-                        split2(v[c][blade_perm(NB, 2 * h)], v[c][blade_perm(NB, 2 * h + 1)]);
-#pragma unroll
-            for (int t3 = 0; t3 < 3; ++t3) {
-                uint32_t d[CHI * NP];
-#pragma unroll
-                for (int h = 0; h < CHI * NP; ++h) d[h] = s[h].t[t3];
-                write_slots(p + split_x_plane(T, t3, 0, 0), d);
-            }
+            for (int h = 0; h < CHI * NP; ++h) d[h] = s[h].t[t3];
+            write_slots(p + split_x_plane(T, t3, 0), d);
         }
     };
 
-    f16 acc[R][NC];
+    f16 acc[R][NPT];
 #pragma unroll
     for (int r = 0; r < R; ++r)
 #pragma unroll
-        for (int n = 0; n < NC; ++n)
+        for (int n = 0; n < NPT; ++n)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[r][n][e] = 0.f;
 
@@ -395,12 +281,12 @@ __global__ __launch_bounds__(64 * WCO * WPOS, 2) void conv_split_kernel(SplitArg
     // loads, goes behind the first fragments' reads, and `convert(0)` and
     // `convert(1)`, the vector work on them, between the MFMAs of the last two
     // regions.
-    constexpr bool HOLD_A = R <= NC;
-    constexpr int NH = HOLD_A ? R : NC, NS = HOLD_A ? NC : R;
+    constexpr bool HOLD_A = R <= NPT;
+    constexpr int NH = HOLD_A ? R : NPT, NS = HOLD_A ? NPT : R;
     auto compute = [&](int slot, int off, auto load, auto convert) {
         auto rd_a = [&](int r, int t) { return frag(fa0 + slot + split_a_plane(T, t, r * RPT, 0)); };
         auto rd_b = [&](int n, int t) {
-            return frag(fb0[n / S] + off + split_x_plane(T, t, n % S, 0));
+            return frag(fb0[n] + off + split_x_plane(T, t, 0));
         };
         b8 H[NH][3], F[2][3];
 #pragma unroll
@@ -562,24 +448,8 @@ __global__ __launch_bounds__(64 * WCO * WPOS, 2) void conv_split_kernel(SplitArg
         for (int e = 0; e < CW / 2; ++e) {
             const int co = split_out_co(T, g, wave, lane, e);
             float v[8];
-            if constexpr (REP && NB == 4) {
-                const float M[4] = {el(0, np * 2, e), el(0, np * 2 + 1, e), el(1, np * 2, e),
-                                    el(1, np * 2 + 1, e)};
-                from_matrix(M, a.rep, v);
-            } else if constexpr (REP) {
-                float M[8];
 #pragma unroll
-                for (int r = 0; r < 2; ++r)
-#pragma unroll
-                    for (int c = 0; c < 2; ++c)
-#pragma unroll
-                        for (int ri = 0; ri < 2; ++ri)
-                            M[2 * (2 * r + c) + ri] = el(2 * r + ri, np * 2 + c, e);
-                from_matrix3(M, v);
-            } else {
-#pragma unroll
-                for (int i = 0; i < NB; ++i) v[blade_perm(NB, i)] = el(i, np, e);
-            }
+            for (int i = 0; i < NB; ++i) v[blade_perm(NB, i)] = el(i, np, e);
             if (m < g.m_end && co < a.C_out) {
                 float z = 0.f;
 #pragma unroll
@@ -603,10 +473,10 @@ __global__ __launch_bounds__(64 * WCO * WPOS, 2) void conv_split_kernel(SplitArg
     }
 }
 
-template <int KD, int NB, int DF, int REP, int WCO, int WPOS, int NPT, int LP, int CW>
+template <int KD, int NB, int DF, int WCO, int WPOS, int NPT, int LP, int CW>
 cliff_status run(const ConvProblem& p, hipStream_t stream, int64_t* blocks)
 {
-    constexpr SplitTile T{KD, NB, REP, WCO, WPOS, NPT, LP, CW};
+    constexpr SplitTile T{KD, NB, WCO, WPOS, NPT, LP, CW};
     static_assert(T.lds_bytes() <= 160 * 1024, "LDS");
     const int64_t D = p.d_image, Do = p.d_out, df = p.d_filter, P = T.pos();
     int64_t npos = 1, img = 1, taps = 1;
@@ -660,7 +530,6 @@ cliff_status run(const ConvProblem& p, hipStream_t stream, int64_t* blocks)
     a.nx = (int)nx;
     a.xi = (int)xi;
     a.cin_stride = (int)img;
-    a.rep = KD == 2 ? split_rep2(p.sign) : 0;
     a.sign = p.sign;
     a.act = p.act;
     for (int i = 0; i < NB; ++i)
@@ -676,15 +545,15 @@ cliff_status run(const ConvProblem& p, hipStream_t stream, int64_t* blocks)
         }
     if (debug_enabled())
         fprintf(stderr,
-                "cliffconv: conv_split k=%d d_filter=%d %s, %d channels x %d positions, "
+                "cliffconv: conv_split k=%d d_filter=%d, %d channels x %d positions, "
                 "%lld workgroups of %d, %d LDS bytes\n",
-                KD, (int)df, REP ? "matrices" : "blades", T.co_wg(), (int)P, (long long)n_blk,
+                KD, (int)df, T.co_wg(), (int)P, (long long)n_blk,
                 T.nt(), T.lds_bytes());
-    if (observe_launch(LAUNCH_CONV_SPLIT, {KD, NB, REP, WCO, WPOS, NPT, LP, CW}, n_blk, T.nt(),
+    if (observe_launch(LAUNCH_CONV_SPLIT, {KD, NB, WCO, WPOS, NPT, LP, CW}, n_blk, T.nt(),
                        T.lds_bytes(), &a))
         return CLIFF_OK;
     clear_hip_error();
-    hipLaunchKernelGGL((conv_split_kernel<KD, NB, DF, REP, WCO, WPOS, NPT, LP, CW>), dim3((unsigned)n_blk),
+    hipLaunchKernelGGL((conv_split_kernel<KD, NB, DF, WCO, WPOS, NPT, LP, CW>), dim3((unsigned)n_blk),
                        dim3(T.nt()), (size_t)T.lds_bytes(), stream, a);
     return hipGetLastError() == hipSuccess ? CLIFF_OK : CLIFF_EDEVICE;
 }
@@ -698,58 +567,33 @@ struct Shape {
     int cpg, cw;
     double t1, t2;
 };
-template <int KD, int NB, int DF, int REP, int WCO, int WPOS, int NPT, int LP, int CW = 32>
+template <int KD, int NB, int DF, int WCO, int WPOS, int NPT, int LP, int CW = 32>
 constexpr Shape shape(double t1, double t2)
 {
-    return Shape{run<KD, NB, DF, REP, WCO, WPOS, NPT, LP, CW>,
-                 SplitTile{KD, NB, REP, WCO, WPOS, NPT, LP, CW}.cpg(), CW, t1, t2};
+    return Shape{run<KD, NB, DF, WCO, WPOS, NPT, LP, CW>,
+                 SplitTile{KD, NB, WCO, WPOS, NPT, LP, CW}.cpg(), CW, t1, t2};
 }
 
 template <int DF>
 cliff_status launch_df(const ConvProblem& p, hipStream_t stream, double most_us)
 {
-    // 64 x 256, 64 x 128, 32 x 256, 32 x 128 (channels x positions; 64 x 64
-    // measured 1.20, 1.70: never ahead of 32 x 128), 16 x 256, 16 x 128
-    static constexpr Shape rep2[] = {
-        shape<2, 4, DF, 1, 2, 4, 2, 320>(2.43, 4.70), shape<2, 4, DF, 1, 2, 2, 2, 148>(1.55, 2.60),
-        shape<2, 4, DF, 1, 1, 8, 1, 320>(1.47, 2.79), shape<2, 4, DF, 1, 1, 4, 1, 148>(1.18, 1.61),
-        shape<2, 4, DF, 1, 1, 8, 1, 320, 16>(0.98, 1.99),
-        shape<2, 4, DF, 1, 1, 4, 1, 148, 16>(0.74, 1.02)};
-    // ... and 64 x 64, 16 x 256 (16 x 128: 62 against 59, 217 against 193 us)
-    static constexpr Shape gen2[] = {
-        shape<2, 4, DF, 0, 2, 4, 2, 320>(2.13, 4.18), shape<2, 4, DF, 0, 2, 2, 2, 168>(1.19, 2.23),
-        shape<2, 4, DF, 0, 1, 8, 1, 320>(1.12, 2.20), shape<2, 4, DF, 0, 1, 4, 1, 168>(0.76, 1.27),
-        shape<2, 4, DF, 0, 2, 2, 1, 100>(0.75, 1.36),
-        shape<2, 4, DF, 0, 1, 8, 1, 320, 16>(0.75, 1.25)};
-    // 32 x 128, 64 x 64, 64 x 128, 16 x 128
-    static constexpr Shape rep3[] = {shape<3, 8, DF, 1, 1, 4, 1, 148>(1.23, 2.27),
-                                     shape<3, 8, DF, 1, 2, 2, 1, 84>(1.25, 2.32),
-                                     shape<3, 8, DF, 1, 2, 4, 1, 288>(2.12, 4.17),
-                                     shape<3, 8, DF, 1, 1, 4, 1, 148, 16>(1.05, 1.41)};
-    // k = 1: 64 x 256, 64 x 128, 64 x 512, 32 x 512, 32 x 256
-    static constexpr Shape gen1[] = {
-        shape<1, 2, 0, 0, 2, 4, 2, 512>(1.70, 3.40), shape<1, 2, 0, 0, 2, 2, 2, 256>(1.08, 1.76),
-        shape<1, 2, 0, 0, 2, 4, 4, 724>(3.10, 6.20), shape<1, 2, 0, 0, 1, 8, 2, 724>(1.78, 3.56),
-        shape<1, 2, 0, 0, 1, 4, 2, 360>(1.10, 1.83)};
-    // 32 x 128, 32 x 256
-    static constexpr Shape gen3[] = {shape<3, 8, DF, 0, 1, 4, 1, 168>(1.48, 2.28),
-                                     shape<3, 8, DF, 0, 1, 8, 1, 320>(2.10, 4.17)};
-    const Shape* s;
-    int n;
-    if (p.k == 1) {
-        s = gen1;
-        n = 5;
-    } else if (p.k == 2) {
-        const bool rep = split_rep2(p.sign) >= 0;
-        s = rep ? rep2 : gen2;
-        n = 6;
-    } else if (split_rep3(p.sign)) {
-        s = rep3;
-        n = 4;
-    } else {
-        s = gen3;
-        n = 2;
-    }
+    // k = 1, channels x positions: 64 x 256, 64 x 128, 64 x 512, 32 x 512, 32 x 256
+    static constexpr Shape shapes1[] = {
+        shape<1, 2, 0, 2, 4, 2, 512>(1.70, 3.40), shape<1, 2, 0, 2, 2, 2, 256>(1.08, 1.76),
+        shape<1, 2, 0, 2, 4, 4, 724>(3.10, 6.20), shape<1, 2, 0, 1, 8, 2, 724>(1.78, 3.56),
+        shape<1, 2, 0, 1, 4, 2, 360>(1.10, 1.83)};
+    // k = 2: 64 x 256, 64 x 128, 32 x 256, 32 x 128, 64 x 64, 16 x 256 (16 x 128
+    // never ahead: 62 against 59, 217 against 193 us)
+    static constexpr Shape shapes2[] = {
+        shape<2, 4, DF, 2, 4, 2, 320>(2.13, 4.18), shape<2, 4, DF, 2, 2, 2, 168>(1.19, 2.23),
+        shape<2, 4, DF, 1, 8, 1, 320>(1.12, 2.20), shape<2, 4, DF, 1, 4, 1, 168>(0.76, 1.27),
+        shape<2, 4, DF, 2, 2, 1, 100>(0.75, 1.36),
+        shape<2, 4, DF, 1, 8, 1, 320, 16>(0.75, 1.25)};
+    // k = 3: 32 x 128, 32 x 256
+    static constexpr Shape shapes3[] = {shape<3, 8, DF, 1, 4, 1, 168>(1.48, 2.28),
+                                        shape<3, 8, DF, 1, 8, 1, 320>(2.10, 4.17)};
+    const Shape* const s = p.k == 1 ? shapes1 : p.k == 2 ? shapes2 : shapes3;
+    const int n = p.k == 1 ? 5 : p.k == 2 ? 6 : 2;
     const int cus = device_cus();
     if (cus < 1) return CLIFF_EUNSUPPORTED;
     // Estimate: the CU with the most workgroups takes them in pairs; a step

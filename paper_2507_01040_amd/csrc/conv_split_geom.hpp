@@ -27,55 +27,35 @@ struct SplitArgs {
     int n_co_blk, n_blk;
     int nx, xi;   // strip rounds of a stage's input, and those of one step
     int cin_stride;  // d_image^k: multivectors between input channels
-    int rep;      // k = 2 matrix representation (split_rep2)
     SignMasks sign;
     uint32_t sx[32], sz[32];  // sign bits and keep masks of two K slots, [i][pair]
     ActParams act;
 };
 
-// The 2x2 matrix representation of a k = 2 table (0: g = (1, 1), 1: (1, -1),
-// 2: (-1, 1); the table's diagonal entries (0, j) hold the squares of the
-// blades), -1 for the others; k = 3: whether g = (1, 1, 1).
-inline int split_rep2(const SignMasks& s)
-{
-    const float g1 = sign_of(s, 1), g2 = sign_of(s, 2);
-    return g1 > 0 && g2 > 0 ? 0 : g1 > 0 && g2 < 0 ? 1 : g1 < 0 && g2 > 0 ? 2 : -1;
-}
-inline bool split_rep3(const SignMasks& s)
-{
-    return sign_of(s, 1) > 0 && sign_of(s, 2) > 0 && sign_of(s, 3) > 0;
-}
-
 // The compile-time shape of one kernel instantiation.  KD spatial dimensions,
-// NB blades; REP: 2x2 matrices stand for the multivectors (else the expanded
-// kernel); WCO x WPOS waves, each 32 output channels by 32 * NPT positions;
-// LP input positions staged per K group; CW output channels a wave, 32 or 16.
-//   R   rows of CW output channels per wave (matrix rows, real and imaginary
-//       parts apart, or output blades); 32 / CW of them fill an MFMA row tile
-//   C   inner index of one input channel (K slots)
-//   S   columns of one position
+// NB blades; WCO x WPOS waves, each CW output channels (32 or 16) by 32 * NPT
+// positions; LP input positions staged per K group.  A wave holds a row of CW
+// output channels for each of the NB output blades; 32 / CW of them fill an
+// MFMA row tile.
 struct SplitTile {
-    int KD, NB, REP, WCO, WPOS, NPT, LP, CW = 32;
-    __host__ __device__ constexpr int R() const { return REP ? NB / 2 : NB; }
+    int KD, NB, WCO, WPOS, NPT, LP, CW = 32;
     __host__ __device__ constexpr int rpt() const { return 32 / CW; }  // rows of a row tile
-    __host__ __device__ constexpr int C() const { return REP ? NB / 2 : NB; }
-    __host__ __device__ constexpr int S() const { return REP ? 2 : 1; }
     __host__ __device__ constexpr int waves() const { return WCO * WPOS; }
     __host__ __device__ constexpr int nt() const { return 64 * waves(); }
     __host__ __device__ constexpr int co_wg() const { return CW * WCO; }
     __host__ __device__ constexpr int pos() const { return 32 * NPT * WPOS; }
     // input channels of one K group (16 slots), of one 8-slot chunk, and of
     // one lane's conversion item (8 slots at most, 8 filter floats at most)
-    __host__ __device__ constexpr int cpg() const { return 16 / C(); }
-    __host__ __device__ constexpr int cpc() const { return 8 / C(); }
-    __host__ __device__ constexpr int chi() const { return C() == 2 ? 2 : 1; }
+    __host__ __device__ constexpr int cpg() const { return 16 / NB; }
+    __host__ __device__ constexpr int cpc() const { return 8 / NB; }
+    __host__ __device__ constexpr int chi() const { return NB == 2 ? 2 : 1; }
     __host__ __device__ constexpr int nchi() const { return cpg() / chi(); }
     __host__ __device__ constexpr int a_items() const { return co_wg() * nchi(); }
     // LDS bytes: two filter slots (one K group of one tap), two input buffers
     __host__ __device__ constexpr int a_plane() const { return co_wg() * 16; }
-    __host__ __device__ constexpr int a_bytes() const { return 3 * R() * 2 * a_plane(); }
+    __host__ __device__ constexpr int a_bytes() const { return 3 * NB * 2 * a_plane(); }
     __host__ __device__ constexpr int x_plane() const { return LP * 16; }
-    __host__ __device__ constexpr int x_bytes() const { return 3 * S() * 2 * x_plane(); }
+    __host__ __device__ constexpr int x_bytes() const { return 3 * 2 * x_plane(); }
     __host__ __device__ constexpr int lds_bytes() const { return 2 * (a_bytes() + x_bytes()); }
 };
 
@@ -83,15 +63,15 @@ struct SplitTile {
 // their number is fixed, else what a lane keeps offsets for.
 __host__ __device__ constexpr int split_rounds(int KD, int DF) { return DF > 0 ? DF : KD == 1 ? 8 : 4; }
 
-// LDS byte offsets of the planes: term t (0 high, 1 middle, 2 low part),
-// matrix row r or column c, chunk g of 8 K slots.
+// LDS byte offsets of the planes: term t (0 high, 1 middle, 2 low part), row
+// (output blade) r, chunk g of 8 K slots.
 __host__ __device__ constexpr int split_a_plane(const SplitTile& T, int t, int r, int g)
 {
-    return ((t * T.R() + r) * 2 + g) * T.a_plane();
+    return ((t * T.NB + r) * 2 + g) * T.a_plane();
 }
-__host__ __device__ constexpr int split_x_plane(const SplitTile& T, int t, int c, int g)
+__host__ __device__ constexpr int split_x_plane(const SplitTile& T, int t, int g)
 {
-    return ((t * T.S() + c) * 2 + g) * T.x_plane();
+    return (t * 2 + g) * T.x_plane();
 }
 
 // One workgroup's block: P consecutive flattened output positions [m0, m_end)
@@ -175,12 +155,12 @@ __host__ __device__ inline int split_rt_off(const SplitArgs& a, int rt)
     const int qz = udiv(rt, a.df);
     return (qz * a.D + (rt - qz * a.df)) * a.D;
 }
-// LDS byte of an item's slots inside the plane group of one (term, column):
-// add split_x_plane(term, column, 0).
+// LDS byte of an item's slots inside the plane group of one term: add
+// split_x_plane(term, 0).
 __host__ __device__ inline int split_x_lds(const SplitTile& T, int chi, int t)
 {
     const int ch = chi * T.chi();
-    return (ch / T.cpc()) * T.x_plane() + t * 16 + (ch % T.cpc()) * T.C() * 2;
+    return (ch / T.cpc()) * T.x_plane() + t * 16 + (ch % T.cpc()) * T.NB * 2;
 }
 
 // Filter item: output channel co0 + e % CO_WG, channels (e / CO_WG) * CHI ...
@@ -199,10 +179,10 @@ __host__ __device__ inline int split_a_goff(const SplitTile& T, const SplitArgs&
 __host__ __device__ inline int split_a_lds(const SplitTile& T, int e)
 {
     const int ch = split_a_chi(T, e) * T.chi();
-    return (ch / T.cpc()) * T.a_plane() + split_a_co(T, e) * 16 + (ch % T.cpc()) * T.C() * 2;
+    return (ch / T.cpc()) * T.a_plane() + split_a_co(T, e) * 16 + (ch % T.cpc()) * T.NB * 2;
 }
 
-// MFMA fragment reads of a lane (add the plane of term and row or column).
+// MFMA fragment reads of a lane (add the plane of the term, and the row's).
 // MFMA row lane % 32 of a row tile is output channel lane % CW of the wave, in
 // row (lane % 32) / CW of the tile's.
 __host__ __device__ inline int split_a_frag(const SplitTile& T, int wave, int lane)

@@ -88,7 +88,7 @@ void walk(const LaunchPlan& p, const SplitTile& T, const SplitArgs& a)
         for (int t = 0; t < KD; ++t) o = o * D + c[t];
         return b * a.C_in * img + o;
     };
-    const int SLOT = T.C() * 2;  // LDS bytes of one channel in one plane
+    const int SLOT = NB * 2;  // LDS bytes of one channel in one plane
     for (int64_t bi = 0; bi < a.n_blk; ++bi) {
         const SplitBlock g = split_block<KD>(T, a, (int)bi);
         if (g.m0 < 0 || g.m_end > a.M || g.m0 >= g.m_end || g.co0 < 0 || g.co0 >= a.C_out) {
@@ -225,8 +225,8 @@ void walk(const LaunchPlan& p, const SplitTile& T, const SplitArgs& a)
         }
     }
     // planes lie one behind the other inside a slot or buffer
-    if (split_a_plane(T, 2, T.R() - 1, 1) + T.a_plane() != T.a_bytes() ||
-        split_x_plane(T, 2, T.S() - 1, 1) + T.x_plane() != T.x_bytes())
+    if (split_a_plane(T, 2, NB - 1, 1) + T.a_plane() != T.a_bytes() ||
+        split_x_plane(T, 2, 1) + T.x_plane() != T.x_bytes())
         fail("plane offsets");
     if (count) {
         const int64_t n = B * a.C_out * a.npos;
@@ -244,8 +244,7 @@ void walk(const LaunchPlan& p, const SplitTile& T, const SplitArgs& a)
 void check_conv_split(const LaunchPlan& p)
 {
     const SplitArgs& a = *static_cast<const SplitArgs*>(p.args);
-    const SplitTile T{p.tpl[0], p.tpl[1], p.tpl[2], p.tpl[3], p.tpl[4], p.tpl[5], p.tpl[6],
-                      p.tpl[7]};
+    const SplitTile T{p.tpl[0], p.tpl[1], p.tpl[2], p.tpl[3], p.tpl[4], p.tpl[5], p.tpl[6]};
     if (T.KD == 1) walk<1>(p, T, a);
     if (T.KD == 2) walk<2>(p, T, a);
     if (T.KD == 3) walk<3>(p, T, a);

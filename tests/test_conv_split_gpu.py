@@ -1,7 +1,7 @@
 """GPU parity of the split-operand convolution kernel (bf16 matrix cores, every
 fp32 operand the sum of three parts), through the automatic choice on layers
-that take it: matrix form and expanded form, every tile shape, ragged channels
-and positions, filter lengths with and without an unrolled kernel, gates, no
+that take it: every tile shape and kind of signature, ragged channels and
+positions, filter lengths with and without an unrolled kernel, gates, no
 bias.  The host bounds checker walks the same launches and asserts their tiles
 (tests/test_split_bounds.py).
 
@@ -22,36 +22,37 @@ pytestmark = pytest.mark.gpu
 
 LIN, SUM, MEAN = P.AGG_LINEAR, P.AGG_SUM, P.AGG_MEAN
 # (g, (B, C_in, C_out, d_image, d_filter), gate (mode, blades) or None, bias,
-#  tile REP.WCO.WPOS.NPT, with .16 where a wave has 16 channels instead of 32)
+#  tile WCO.WPOS.NPT, with .16 where a wave has 16 channels instead of 32)
 CASES = [
-    ((1, 1), (4, 9, 62, 130, 3), None, True, "1.2.4.2"),
-    ((1, 1), (1, 8, 64, 300, 3), (LIN, (0, 1, 2, 3)), True, "1.2.2.2"),
-    ((1, -1), (3, 13, 61, 93, 3), None, False, "1.1.8.1"),
-    ((-1, 1), (1, 24, 64, 128, 3), (MEAN, (3,)), True, "1.1.4.1"),
-    ((-1, 1), (6, 16, 32, 67, 7), (LIN, (1, 3)), True, "1.1.8.1"),
-    ((1, 1), (7, 16, 64, 98, 2), (SUM, (2, 1)), True, "1.2.2.2"),
-    ((1, -1), (6, 13, 61, 90, 5), None, False, "1.2.4.2"),
-    ((-1, 0), (4, 9, 62, 127, 3), (MEAN, (0, 2)), True, "0.2.4.2"),
-    ((-1, -1), (1, 24, 64, 128, 3), None, True, "0.2.2.1"),
-    ((0, 1), (1, 8, 64, 300, 3), (LIN, (3, 0, 1)), True, "0.1.8.1"),
-    ((-1, -1), (6, 13, 61, 90, 5), None, False, "0.1.4.1"),
-    ((1, 1, 1), (2, 16, 32, 26, 3), (MEAN, tuple(range(8))), True, "1.1.4.1"),
-    ((1, 1, 1), (40, 8, 29, 12, 3), (LIN, (7, 0, 3)), True, "1.2.2.1"),
-    ((1, 1, 1), (64, 7, 60, 10, 3), None, False, "1.2.4.1"),
-    ((1, -1, 1), (8, 6, 20, 34, 3), None, True, "0.1.8.1"),
-    ((0, 0, 1), (64, 7, 60, 10, 3), (SUM, (4, 1)), True, "0.1.4.1"),
-    ((-1,), (2000, 21, 62, 61, 17), (LIN, (1, 0)), True, "0.2.2.2"),
-    ((1,), (700, 32, 64, 260, 5), None, False, "0.2.4.2"),
-    ((-1,), (1024, 13, 64, 515, 9), (MEAN, (1,)), True, "0.2.4.4"),
-    ((-1,), (5800, 32, 30, 60, 17), (SUM, (0, 1)), True, "0.1.8.2"),
-    ((1,), (512, 93, 96, 200, 5), None, True, "0.1.4.2"),
-    ((1, 1), (5, 13, 16, 258, 3), (LIN, (0, 1, 2, 3)), True, "1.1.8.1.16"),
-    ((-1, 1), (3, 24, 11, 131, 5), None, True, "1.1.8.1.16"),
-    ((1, -1), (9, 64, 16, 67, 3), (SUM, (3, 1)), False, "1.1.8.1.16"),
-    ((-1, 0), (5, 13, 15, 258, 3), (MEAN, (0, 2)), True, "0.1.8.1.16"),
-    ((1, 1), (4, 8, 16, 300, 3), None, True, "1.1.4.1.16"),
-    ((1, 1, 1), (5, 7, 16, 34, 3), (LIN, (7, 0, 3)), True, "1.1.4.1.16"),
-    ((1, 1, 1), (5, 16, 13, 34, 2), None, False, "1.1.4.1.16"),
+    ((1, 1), (4, 9, 62, 130, 3), None, True, "2.4.2"),
+    ((1, 1), (1, 8, 64, 300, 3), (LIN, (0, 1, 2, 3)), True, "1.8.1"),
+    ((1, -1), (10, 13, 61, 93, 3), None, False, "1.8.1"),
+    ((-1, 1), (1, 24, 64, 128, 3), (MEAN, (3,)), True, "2.2.1"),
+    ((-1, 1), (12, 16, 32, 67, 7), (LIN, (1, 3)), True, "1.8.1"),
+    ((1, 1), (12, 16, 64, 98, 2), (SUM, (2, 1)), True, "2.4.2"),
+    ((1, -1), (6, 13, 61, 90, 5), None, False, "1.4.1"),
+    ((1, 1), (103, 7, 64, 19, 5), None, True, "2.2.2"),
+    ((-1, 0), (4, 9, 62, 127, 3), (MEAN, (0, 2)), True, "2.4.2"),
+    ((-1, -1), (1, 24, 64, 128, 3), None, True, "2.2.1"),
+    ((0, 1), (1, 8, 64, 300, 3), (LIN, (3, 0, 1)), True, "1.8.1"),
+    ((-1, -1), (6, 13, 61, 90, 5), None, False, "1.4.1"),
+    ((1, 1, 1), (2, 16, 32, 26, 3), (MEAN, tuple(range(8))), True, "1.4.1"),
+    ((1, 1, 1), (128, 8, 29, 12, 3), (LIN, (7, 0, 3)), True, "1.8.1"),
+    ((1, 1, 1), (64, 7, 60, 10, 3), None, False, "1.4.1"),
+    ((1, 1, 1), (5, 7, 32, 34, 3), (LIN, (7, 0, 3)), True, "1.4.1"),
+    ((1, 1, 1), (9, 15, 29, 34, 2), None, False, "1.8.1"),
+    ((1, -1, 1), (8, 6, 20, 34, 3), None, True, "1.8.1"),
+    ((0, 0, 1), (64, 7, 60, 10, 3), (SUM, (4, 1)), True, "1.4.1"),
+    ((-1,), (2000, 21, 62, 61, 17), (LIN, (1, 0)), True, "2.2.2"),
+    ((1,), (700, 32, 64, 260, 5), None, False, "2.4.2"),
+    ((-1,), (1024, 13, 64, 515, 9), (MEAN, (1,)), True, "2.4.4"),
+    ((-1,), (5800, 32, 30, 60, 17), (SUM, (0, 1)), True, "1.8.2"),
+    ((1,), (512, 93, 96, 200, 5), None, True, "1.4.2"),
+    ((1, 1), (5, 13, 16, 258, 3), (LIN, (0, 1, 2, 3)), True, "1.8.1.16"),
+    ((-1, 1), (8, 24, 11, 131, 5), None, True, "1.8.1.16"),
+    ((1, -1), (8, 32, 16, 182, 3), (SUM, (3, 1)), False, "1.8.1.16"),
+    ((-1, 0), (5, 13, 15, 258, 3), (MEAN, (0, 2)), True, "1.8.1.16"),
+    ((1, 1), (4, 8, 16, 300, 3), None, True, "1.8.1.16"),
 ]
 IDS = ["%s-%s" % ("".join(str(v) for v in g), "x".join(str(v) for v in s)) for g, s, _, _, _ in CASES]
 
@@ -106,17 +107,18 @@ def test_conv_split(case):
 @pytest.mark.parametrize("g,shape", [
     ((1, 1), (1, 8, 64, 300, 3)), ((-1, 0), (1, 8, 64, 300, 3)), ((1, 1, 1), (2, 16, 32, 26, 3)),
     ((1, -1, 1), (2, 16, 32, 26, 3)), ((1, 1), (4, 8, 16, 300, 3)), ((-1, 0), (4, 8, 16, 300, 3)),
-    ((1, 1, 1), (4, 16, 16, 34, 3))], ids=str)
+    ((1, 1, 1), (4, 16, 32, 34, 3))], ids=str)
 def test_conv_split_non_finite(g, shape):
     # infinities, NaN, the largest floats and products past them: outputs that
-    # bf16 parts or sums of matrix elements cannot hold are those of the
-    # vector kernel, the others are untouched
+    # bf16 parts cannot hold are those of the vector kernel, the others are
+    # untouched
     k = len(g)
     x, f, b, _ = _inputs(g, shape, None, True, 77)
     big = np.float32(3.3e38)
     x[(0, 3) + (4,) * k] = np.inf
     x[(0, 2) + (9,) * k + (1,)] = np.nan
-    x[(0, 1) + (14,) * k] = big            # sums of blades overflow, outputs do not
+    x[(0, 1) + (14,) * k] = big
+    x[(0, 5) + (24,) * k] = 3.4028235e38    # its high bf16 part is infinite, outputs are not
     x[(0, 4) + (20,) * k + (0,)] = -np.inf
     f[(0, 5) + (1,) * k] = 0.0              # zero filter against the values above
     f[(3, 6) + (0,) * k + (1,)] = 0.0
@@ -143,3 +145,44 @@ def test_conv_split_non_finite(g, shape):
     usual = ok & (np.abs(r) < 1e3)
     assert np.max(np.abs(y[usual].astype(np.float64) - r[usual])) <= \
         2.0 ** -22 * np.sqrt(n) * np.max(np.abs(r[usual]))
+
+
+# Layers whose blades differ in size, of every kind of signature: every blade
+# keeps its own digits.
+SCALED = [((1, 1), (1, 8, 64, 300, 3)), ((1, -1), (10, 13, 61, 93, 3)), ((-1, 1), (12, 16, 32, 67, 7)),
+          ((-1, -1), (1, 24, 64, 128, 3)), ((1, 1), (4, 8, 16, 300, 3)),
+          ((1, 1, 1), (2, 16, 32, 26, 3)), ((1, -1, 1), (8, 6, 20, 34, 3)),
+          ((-1,), (2000, 21, 62, 61, 17))]
+
+
+@pytest.mark.parametrize("even", [False, True], ids=["scalar", "even"])
+@pytest.mark.parametrize("g,shape", SCALED, ids=str)
+def test_conv_split_blades_of_different_size(g, shape, even):
+    # inputs with blades 1e4, 1, 1, 1e-4, ... and filters of blade 0 (or of the
+    # even blades, the others zero).  Each of the 6 C_in N_B / 16 accumulations
+    # of a tap loses at most 2^-23 of a partial sum, and no partial sum of a
+    # blade is far above the blade's largest output; the error of every blade
+    # also stays within three times the fp32 kernel's.
+    k = len(g)
+    nb = 1 << k
+    print(g, shape, even, flush=True)
+    x, f, _, _ = _inputs(g, shape, None, False, 31)
+    grade = [0, 1] if k == 1 else [0, 1, 1, 2] if k == 2 else [0, 1, 1, 1, 2, 2, 2, 3]
+    for i in range(nb):
+        x[..., i] *= np.float32(10.0 ** (4 - 4 * grade[i]) if k > 1 else (1e4, 1e-4)[i])
+        if grade[i] % 2 or (i and not even):
+            f[..., i] = 0.0
+        elif i:
+            f[..., i] *= np.float32(1e-4)
+    y = _run(g, x, f, None, None, P.ALGO_AUTO)
+    sel = sorted({0, shape[0] - 1})
+    ref = oracle.conv_nd(x[sel], f, np.zeros((shape[2], nb), np.float32), g)
+    z = _run(g, x, f, None, None, P.ALGO_MFMA)
+    e, ez = (np.abs(v[sel] - ref).reshape(-1, nb).max(0) for v in (y, z))
+    size = np.abs(ref).reshape(-1, nb).max(0)
+    assert (size > 0).sum() >= nb // 2
+    print("error over the blade's largest", e / np.maximum(size, 1e-300), "fp32 kernel",
+          ez / np.maximum(size, 1e-300), flush=True)
+    n_acc = 6 * -(-shape[1] * nb // 16) * shape[4] ** k
+    assert (e <= n_acc * 2.0 ** -23 * size).all()
+    assert (e <= 3 * ez).all()

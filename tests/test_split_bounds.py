@@ -28,7 +28,7 @@ def test_parity_cases():
         f = res.split()
         assert f[0] == "ok" and f[4] == "7", (g, shape, res)
         t = f[5].split(".")
-        assert ".".join(t[2:6] + (["16"] if t[7] == "16" else [])) == tile, (g, shape, res)
+        assert ".".join(t[2:5] + (["16"] if t[6] == "16" else [])) == tile, (g, shape, res)
 
 
 def test_benchmark_layers_and_sizes():
