@@ -146,7 +146,7 @@ typedef enum {
     CLIFF_ALGO_MFMA_NARROW = 5, /* MFMA, 8 / 8 / 4 channels x 256 positions */
     CLIFF_ALGO_MFMA_TINY = 6,   /* MFMA, 8 / 4 / 2 channels x 32 positions
                                    (k = 2, 3: the K loop split over 4 waves) */
-    CLIFF_ALGO_MFMA_STREAM = 7  /* MFMA, linear layers only (d_image =
+    CLIFF_ALGO_MFMA_STREAM = 7  /* fp32 MFMA, linear layers only (d_image =
                                    d_filter = 1, C_in N_B and C_out N_B each
                                    64, 128 or 256): persistent waves that
                                    stream 16-64 positions at a time past the
@@ -181,7 +181,10 @@ cliff_status clifford_conv_nd_algo(int k, const int8_t* g, int64_t B,
  * Same alignment, size, error and stream rules as clifford_conv_nd; it is
  * the convolution with d_image = d_filter = 1.  Layers with C_in N_B and
  * C_out N_B each 64, 128 or 256 and B >= 16384 run on a streamed kernel that
- * keeps the weight in LDS (CLIFF_ALGO_MFMA_STREAM); other layers on the
+ * keeps the weight in LDS: on fp32 MFMA (CLIFF_ALGO_MFMA and
+ * CLIFF_ALGO_MFMA_STREAM), or, by the automatic choice and for C_in N_B ->
+ * C_out N_B = 128 -> 128, 64 -> 128, 128 -> 64 and 256 -> 64, on bf16 MFMA with
+ * every fp32 operand as the sum of three bf16 parts.  Other layers run on the
  * convolution kernels.
  */
 cliff_status clifford_linear(int k, const int8_t* g, int64_t B, int64_t C_in,

@@ -168,9 +168,11 @@ ActParams to_params(const cliff_act_desc* act)
     return a;
 }
 
-// Linear layers: the streamed kernel from 16384 rows on (measured on MI355X
-// over 7 widths: from there it beats every convolution tile; below, the
-// tiny and medium tiles are 1-4 us faster).
+// Linear layers: the streamed kernels from 16384 rows on (measured on MI355X
+// over 7 widths: from there the fp32 one beats every convolution tile; below,
+// the tiny and medium tiles are 1-4 us faster).  The split one goes first where
+// it has the width (16384 rows of 32 -> 32 channels: 15.2 -> 14.5 us; its
+// workgroups each expand the weight first), for the automatic choice only.
 bool linear_stream_pays(const ConvProblem& p)
 {
     return p.B >= 16 * 1024;
@@ -241,7 +243,9 @@ cliff_status clifford_conv_nd_algo(int k, const int8_t* g, int64_t B, int64_t C_
     if (algo == CLIFF_ALGO_MFMA_STREAM) return launch_linear_mfma(p, st);
     if ((algo == CLIFF_ALGO_AUTO || algo == CLIFF_ALGO_MFMA) && d_image == 1 &&
         linear_stream_pays(p)) {
-        const cliff_status s = launch_linear_mfma(p, st);
+        cliff_status s = CLIFF_EUNSUPPORTED;
+        if (algo == CLIFF_ALGO_AUTO) s = launch_linear_split(p, st);
+        if (s == CLIFF_EUNSUPPORTED) s = launch_linear_mfma(p, st);
         if (s != CLIFF_EUNSUPPORTED) return s;
     }
     if (algo == CLIFF_ALGO_AUTO) {

@@ -450,12 +450,6 @@ cliff_status run_linear_nk(const ConvProblem& p, hipStream_t stream)
 cliff_status launch_linear_mfma(const ConvProblem& p, hipStream_t stream)
 {
     if (p.d_image != 1 || p.d_filter != 1) return CLIFF_EUNSUPPORTED;
-    // the split kernel from where it is the faster one (16384 rows of 32 -> 32
-    // channels: 15.2 -> 14.5 us; its workgroups each expand the weight first)
-    if (p.B >= 16384) {
-        const cliff_status s = launch_linear_split(p, stream);
-        if (s != CLIFF_EUNSUPPORTED) return s;
-    }
     switch (p.nb) {
         case 2: return run_linear_nk<2>(p, stream);
         case 4: return run_linear_nk<4>(p, stream);

@@ -157,10 +157,11 @@ def test_stream_linear_no_bias():
 
 
 def test_auto_choice_matches_forced_stream():
-    # clifford_linear picks the streamed kernel for this size; both runs must
-    # be bit-identical (same kernel, no atomics)
+    # clifford_linear picks the streamed kernel for this size and width (64 to
+    # 64 columns; 128 go to the split kernel, which no forced choice takes);
+    # both runs must be bit-identical (same kernel, no atomics)
     g = (1, 1)
-    x, w, b = _inputs(900, 40000, 32, 4)
+    x, w, b = _inputs(900, 40000, 16, 4)
     y1, _ = _run(g, x, w, b, algo=P.ALGO_MFMA_STREAM)
     y2, _ = _run(g, x, w, b, algo=P.ALGO_AUTO)
     assert np.array_equal(y1, y2)

@@ -59,21 +59,23 @@ def test_observer_without_the_kind():
 
 
 def test_linear_layers():
-    # the split linear kernel, automatic and forced streamed: the GPU tests'
-    # layers and the benchmark's; smaller batches and other widths stay with
-    # the fp32 kernels
+    # the automatic choice takes the split linear kernel for the GPU tests'
+    # layers and the benchmark's, and keeps the fp32 kernels for smaller batches
+    # and other widths; the forced choices (fp32 tiles, streamed) stay with the
+    # fp32 streamed kernel at every batch size
     import test_linear_split_gpu as T
     S = P.ALGO_MFMA_STREAM
-    cases = [(g, B, ci, co, gate, "8") for g, B, ci, co, gate, _ in T.CASES]
-    cases += [((1, 1), 1 << 20, 32, 32, None, "8"), ((1, 1), T.B0 - 1, 32, 32, None, None),
-              ((1,), 1 << 21, 32, 32, None, "4"), ((1, 1), 1 << 18, 24, 32, None, "1")]
+    cases = [(g, B, ci, co, gate, "8", "4", "4") for g, B, ci, co, gate, _ in T.CASES]
+    cases += [((1, 1), 1 << 20, 32, 32, None, "8", "4", "4"),
+              ((1, 1), T.B0 - 1, 32, 32, None, "1", "1", "4"),
+              ((1,), 1 << 21, 32, 32, None, "4", "4", "4"),
+              ((1, 1), 1 << 18, 24, 32, None, "1", "1", None)]
     lines, want = [], []
-    for g, B, ci, co, gate, kind in cases:
-        for algo in (P.ALGO_AUTO, S):
-            if kind == "1" and algo == S:
-                continue
-            lines.append(conv_line(len(g), g, B, ci, co, 1, 1, algo, gate))
-            want.append(kind or ("1" if algo == P.ALGO_AUTO else "4"))
+    for g, B, ci, co, gate, *kinds in cases:
+        for algo, kind in zip((P.ALGO_AUTO, P.ALGO_MFMA, S), kinds):
+            if kind is not None:
+                lines.append(conv_line(len(g), g, B, ci, co, 1, 1, algo, gate))
+                want.append(kind)
     out = HC.run(["kinds 8"] + lines)[1:]
     for line, res, kind in zip(lines, out, want):
         f = res.split()
