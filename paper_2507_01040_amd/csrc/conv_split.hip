@@ -40,7 +40,7 @@
 // first fragments' reads.  Measured against the fp32 tiles: k = 2, B 8, C 64,
 // d 128, 3x3 1078 -> 601 us; k = 3, B 8, C 32, d 32 5426 -> 3550 us; C 64, d 36
 // 30.9 -> 17.8 ms; k = 1, B 4096, C 64, d 60, 17 taps 712 -> 510 us.  The error
-// against 64 bits falls from 8.6e-7 to 5.2e-7 (2-norm, 2304 products), as 16
+// against 64 bits falls from 8.6e-7 to 7.4e-7 (2-norm, 2304 products), as 16
 // products go into one rounding; where most products are zero (filters of one
 // blade) it is up to twice the fp32 tiles', six roundings to their four.
 // Tried on the 2 x 2 matrix form: 16x16x32 MFMAs with two products of parts in
@@ -50,9 +50,13 @@
 // instead of at the start of a step (360 -> 397 us), all taps of a row loaded at
 // once (360 -> 369 us).
 //
-// Values that bf16 arithmetic cannot carry (infinities, sums past the largest
-// float) come out non-finite; such outputs are computed again, by the lane
-// that holds them, as plain fp32 sums.
+// Values that bf16 arithmetic cannot carry (infinities, the largest floats, sums
+// past them) come out non-finite; a wave that holds such a sum computes all of
+// its sums again on the fp32 matrix cores (split_fp32_sums).  With a channel of
+// the lowest value in 7 of 8 images C 64, d 128 takes 1.79 ms (fp32 tiles 1.08;
+// with half of the images masked and one lane for an output 16.3 ms), k = 1,
+// B 1024, C 64, d 60, 17 taps 0.58 ms (0.21; 7.3), k = 3, C 32, d 32, B 2 2.8 ms
+// (1.4; 95).
 #include <stdio.h>
 
 #include <algorithm>
@@ -76,40 +80,97 @@ typedef __bf16 b8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u4 __attribute__((ext_vector_type(4)));
 
-// One output multivector as plain fp32 sums.
-template <int KD, int NB>
-__device__ void plain_output(const SplitArgs& a, int m, int co, float (&v)[8])
+// A wave's accumulators as sums of fp32 products on the fp32 matrix cores, for
+// values that bf16 parts cannot hold: operands straight from memory, one tap of
+// one input channel at a time and the next one's loads ahead of it.
+template <int KD, int NB, int R, int NPT>
+__device__ void split_fp32_sums(const SplitTile& T, const SplitArgs& a, const SplitBlock& g,
+                                int wave, int lane, f16 (&acc)[R][NPT])
 {
-    const int b = m / a.npos;
-    int p = m - b * a.npos;
-    int64_t off = 0, cs = 1;  // first input position, channel stride
-    int64_t st = 1;
-    for (int t = 0; t < KD; ++t) {
-        off += (int64_t)(p % a.Do) * st;
-        p /= a.Do;
-        st *= a.D;
-        cs *= a.D;
-    }
-    for (int i = 0; i < NB; ++i) v[i] = 0.f;
-    for (int ci = 0; ci < a.C_in; ++ci) {
-        const float* xb = a.x + (((int64_t)b * a.C_in + ci) * cs + off) * NB;
-        const float* wb = a.w + ((int64_t)ci * a.C_out + co) * a.taps * NB;
-        for (int q = 0; q < a.taps; ++q) {
-            int64_t qo = 0, qs = 1;
-            for (int t = 0, r = q; t < KD; ++t) {
-                qo += (int64_t)(r % a.df) * qs;
-                r /= a.df;
-                qs *= a.D;
+    constexpr int RPT = NB / R;
+    // MFMA row lane % 32 is output blade RPT r + hi, K slot lane / 32 of product
+    // h input blade 2 h + jl (bitmasks): filter blade (RPT r ^ 2 h) ^ hi ^ jl
+    const int hi = (lane & 31) / T.CW, jl = lane >> 5;
+    const bool odd = hi ^ jl;
+    float sg[R][NB / 2];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int h = 0; h < NB / 2; ++h)
+            sg[r][h] = sign_of(a.sign, blade_perm(NB, RPT * r + hi) * NB + blade_perm(NB, 2 * h + jl));
+    const float* const wp = a.w + split_redo_w(T, a, g, wave, lane) * NB;
+    const float* xp[NPT];
+#pragma unroll
+    for (int np = 0; np < NPT; ++np)
+        xp[np] = a.x + (g.base + split_redo_x<KD>(T, a, g, wave, lane, np)) * NB;
+    auto load = [&](const float* p, float (&v)[NB]) {
+        if constexpr (NB == 2) {
+            const f2 q = *reinterpret_cast<const f2*>(p);
+            v[0] = q[0];
+            v[1] = q[1];
+        } else {
+#pragma unroll
+            for (int h = 0; h < NB / 4; ++h) {
+                const f4 q = reinterpret_cast<const f4*>(p)[h];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[4 * h + e] = q[e];
             }
-            for (int i = 0; i < NB; ++i)
-                for (int j = 0; j < NB; ++j)
-                    v[i] = fmaf(sign_of(a.sign, i * NB + j) * wb[q * NB + src_blade(NB, i, j)],
-                                xb[qo * NB + j], v[i]);
-            bool nan = true;
-            for (int i = 0; i < NB; ++i) nan = nan && v[i] != v[i];
-            if (nan) return;
         }
-    }
+    };
+    // PD taps in flight: the few products of small multivectors do not cover a
+    // load's latency
+    constexpr int PD = NB == 2 ? 4 : NB == 4 ? 2 : 1;
+    float w[PD][NB], x[PD][NPT][NB];
+    int ci = 0, rt = 0, qx = 0;  // the tap to be loaded next
+    auto load_tap = [&](float (&wt)[NB], float (&xt)[NPT][NB]) {
+        if (ci >= a.C_in) return;
+        const int64_t xo = (int64_t)ci * a.cin_stride + split_rt_off<KD>(a, rt) + qx;
+        load(wp + ((int64_t)ci * a.C_out * a.taps + rt * a.df + qx) * NB, wt);
+#pragma unroll
+        for (int np = 0; np < NPT; ++np) load(xp[np] + xo * NB, xt[np]);
+        if (++qx == a.df) {
+            qx = 0;
+            if (++rt == a.nrt) {
+                rt = 0;
+                ++ci;
+            }
+        }
+    };
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int np = 0; np < NPT; ++np)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[r][np][e] = 0.f;
+#pragma unroll
+    for (int d = 0; d < PD; ++d) load_tap(w[d], x[d]);
+    const int n = a.C_in * a.taps;
+    for (int t0 = 0; t0 < n; t0 += PD)
+#pragma unroll
+        for (int d = 0; d < PD; ++d) {
+            if (t0 + d >= n) break;
+            float wo[NB], xo[NPT][NB / 2];
+#pragma unroll
+            for (int e = 0; e < NB; ++e)
+                wo[e] = odd ? w[d][blade_perm(NB, e ^ 1)] : w[d][blade_perm(NB, e)];
+#pragma unroll
+            for (int np = 0; np < NPT; ++np)
+#pragma unroll
+                for (int h = 0; h < NB / 2; ++h)
+                    xo[np][h] =
+                        jl ? x[d][np][blade_perm(NB, 2 * h + 1)] : x[d][np][blade_perm(NB, 2 * h)];
+            load_tap(w[d], x[d]);
+#pragma unroll
+            for (int h = 0; h < NB / 2; ++h)
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const float f = sg[r][h] * wo[(RPT * r) ^ (2 * h)];
+#pragma unroll
+                    for (int np = 0; np < NPT; ++np)
+                        acc[r][np] =
+                            __builtin_amdgcn_mfma_f32_32x32x2f32(f, xo[np][h], acc[r][np], 0, 0, 0);
+                }
+        }
 }
 
 template <int KD, int NB, int DF, int WCO, int WPOS, int NPT, int LP, int CW>
@@ -407,68 +468,58 @@ __global__ __launch_bounds__(64 * WCO * WPOS, 2) void conv_split_kernel(SplitArg
         cur = nst;
     }
 
-    // Epilogue: back to blades, bias, optional activation; one lane holds a
-    // whole multivector.
+    // Infinite or NaN sums (parts of infinities and of the largest floats, sums
+    // past them): every row of a multivector is in this wave, so a filter blade
+    // dropped with its zero sign shows in the row where its sign is not zero.
+    float z = 0.f;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int n = 0; n < NPT; ++n)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) z = fmaf(acc[r][n][e], 0.f, z);
+    if (__ballot(z != 0.f)) split_fp32_sums<KD, NB>(T, a, g, wave, lane, acc);
+
+    // Epilogue: bias, optional activation; one lane holds a whole multivector.
     const bool has_act = a.act.mode >= 0;
     int gslot[NB];
 #pragma unroll
     for (int i = 0; i < NB; ++i) gslot[i] = has_act ? gate_slot(a.act, i) : -1;
     const FastDiv fnpos = fast_div(a.npos);
-    auto finish = [&](float (&v)[8], int m, int co) {
-        if (a.bias) {
-#pragma unroll
-            for (int i = 0; i < NB; ++i) v[i] += a.bias[co * NB + i];
-        }
-        if (has_act) {
-            float part = 0.f;
-#pragma unroll
-            for (int i = 0; i < NB; ++i) part += gate_coef(a.act, gslot[i], co) * v[i];
-            const float gate = gate_sigmoid(a.act, part, co);
-#pragma unroll
-            for (int i = 0; i < NB; ++i) v[i] *= gate;
-        }
-        float* const yp = a.y + split_out_ofs(a, fnpos, m, co) * NB;
-        if constexpr (NB == 2) {
-            *reinterpret_cast<f2*>(yp) = f2{v[0], v[1]};
-        } else {
-#pragma unroll
-            for (int h = 0; h < NB / 4; ++h)
-                reinterpret_cast<f4*>(yp)[h] = f4{v[4 * h], v[4 * h + 1], v[4 * h + 2], v[4 * h + 3]};
-        }
-    };
     // element e of row r: with 16 channels to a row, odd rows are the row
     // tile's upper half
     auto el = [&](int r, int n, int e) { return acc[r / RPT][n][e + r % RPT * (CW / 2)]; };
-    uint32_t bad[NPT];
 #pragma unroll
     for (int np = 0; np < NPT; ++np) {
         const int m = split_out_m(T, g, wave, lane, np);
-        bad[np] = 0;
 #pragma unroll
         for (int e = 0; e < CW / 2; ++e) {
             const int co = split_out_co(T, g, wave, lane, e);
-            float v[8];
+            if (m >= g.m_end || co >= a.C_out) continue;
+            float v[NB];
 #pragma unroll
             for (int i = 0; i < NB; ++i) v[blade_perm(NB, i)] = el(i, np, e);
-            if (m < g.m_end && co < a.C_out) {
-                float z = 0.f;
+            if (a.bias) {
 #pragma unroll
-                for (int i = 0; i < NB; ++i) z = fmaf(v[i], 0.f, z);
-                if (z != 0.f) bad[np] |= 1u << e;  // a blade is infinite or NaN
-                finish(v, m, co);
+                for (int i = 0; i < NB; ++i) v[i] += a.bias[co * NB + i];
             }
-        }
-    }
+            if (has_act) {
+                float part = 0.f;
 #pragma unroll
-    for (int np = 0; np < NPT; ++np) {
-        const int m = split_out_m(T, g, wave, lane, np);
-        while (bad[np]) {
-            const int e = __builtin_ctz(bad[np]);
-            bad[np] &= bad[np] - 1;
-            const int co = split_out_co(T, g, wave, lane, e);
-            float v[8];
-            plain_output<KD, NB>(a, m, co, v);
-            finish(v, m, co);
+                for (int i = 0; i < NB; ++i) part += gate_coef(a.act, gslot[i], co) * v[i];
+                const float gate = gate_sigmoid(a.act, part, co);
+#pragma unroll
+                for (int i = 0; i < NB; ++i) v[i] *= gate;
+            }
+            float* const yp = a.y + split_out_ofs(a, fnpos, m, co) * NB;
+            if constexpr (NB == 2) {
+                *reinterpret_cast<f2*>(yp) = f2{v[0], v[1]};
+            } else {
+#pragma unroll
+                for (int h = 0; h < NB / 4; ++h)
+                    reinterpret_cast<f4*>(yp)[h] =
+                        f4{v[4 * h], v[4 * h + 1], v[4 * h + 2], v[4 * h + 3]};
+            }
         }
     }
 }

@@ -197,6 +197,24 @@ __host__ __device__ inline int split_b_frag(const SplitTile& T, const SplitArgs&
     return (lane >> 5) * T.x_plane() + split_run(a, g, m) * 16;
 }
 
+// The same product in fp32 (split_fp32_sums): multivector offset of the filters
+// of MFMA row lane % 32 (channel 0, tap 0) and, from the block's base, of the
+// input of column tile np (channel 0, tap 0), both of the last channel or
+// position where the lane's own is past the end.
+__host__ __device__ inline int64_t split_redo_w(const SplitTile& T, const SplitArgs& a,
+                                                const SplitBlock& g, int wave, int lane)
+{
+    const int co = g.co0 + (wave % T.WCO) * T.CW + lane % T.CW;
+    return (int64_t)(co < a.C_out ? co : a.C_out - 1) * a.taps;
+}
+template <int KD>
+__host__ __device__ inline int split_redo_x(const SplitTile& T, const SplitArgs& a,
+                                            const SplitBlock& g, int wave, int lane, int np)
+{
+    const int m = g.m0 + ((wave / T.WCO) * T.NPT + np) * 32 + (lane & 31);
+    return split_x_goff<KD>(a, g, split_run(a, g, m));
+}
+
 // Output channel of accumulator register r (0..CW / 2 - 1, of a row tile's first
 // row) and position of column tile np of a lane.
 __host__ __device__ inline int split_out_co(const SplitTile& T, const SplitBlock& g, int wave,

@@ -23,8 +23,10 @@
 // of 4: 242.  64 -> 256 columns spill (8 row tiles) and stay there, as do
 // 64 -> 64, at the memory's rate already, and 256 -> 256.
 //
-// Rows whose result is not finite (bf16 parts cannot hold infinities) are
-// computed again as plain fp32 sums after the wave's last tile.
+// Tiles with a result that is not finite (bf16 parts cannot hold infinities) are
+// computed again on the fp32 matrix cores after the wave's last one: with a
+// channel of the lowest value in all rows 2^17 rows of 32 -> 32 channels take 96
+// us instead of 38 (half of 2^18 rows, one lane for an output: 437 us).
 #include <stdio.h>
 
 #include <algorithm>
@@ -185,16 +187,10 @@ __global__ __launch_bounds__(512, 2) void linear_split_kernel(LinSplitArgs a)
         if (mean) s = s / (float)a.act.K;
         return 1.0f / (1.0f + __expf(-s));
     };
-    float z = 0.f;  // not zero once an output of this lane is infinite or NaN
-    {
-        const __amdgpu_buffer_rsrc_t d = x_desc(t0);
-#pragma unroll
-        for (int p = 0; p < PF; ++p) load(d, p, ring[p]);
-    }
-    int64_t t = t0, tn = t + stride;
-    tile(t, tn < a.n_tile ? tn : t);
-    for (;;) {
-        const bool more = tn < a.n_tile;
+    // Tile t's outputs from the accumulators; whether one of them is infinite or
+    // NaN (in any lane).
+    auto finish = [&](int64_t t) {
+        float z = 0.f;
         const __amdgpu_buffer_rsrc_t yd = __builtin_amdgcn_make_buffer_rsrc(
             a.y + 32 * t * N, (short)0, lsp_rows(a, t) * N * 4, 0x00020000);
         // the bias and gate parameters are the same for every tile; an opaque
@@ -208,76 +204,77 @@ __global__ __launch_bounds__(512, 2) void linear_split_kernel(LinSplitArgs a)
         for (int r = 0; r < RT; ++r)
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
-              f4 o[2];
+                f4 o[2];
 #pragma unroll
-              for (int h = 0; h < 2; ++h) {
-                const int q = 2 * u + h, n = lsp_y_col(S, lane, r, q);
-                const f4 bb = *reinterpret_cast<const f4*>(ble + n);
-                f4& v = o[h];
-                v = f4{acc[r][4 * q], acc[r][4 * q + 1], acc[r][4 * q + 2], acc[r][4 * q + 3]} + bb;
-                if (has_act) {
-                    const f4 cf = *reinterpret_cast<const f4*>(cle + n);
-                    if constexpr (NB == 2) {
-                        const float g0 = gate(cf[0] * v[0] + cf[1] * v[1], gle, n / 2);
-                        const float g1 = gate(cf[2] * v[2] + cf[3] * v[3], gle, n / 2 + 1);
-                        v[0] *= g0;
-                        v[1] *= g0;
-                        v[2] *= g1;
-                        v[3] *= g1;
-                    } else {
-                        float part = cf[0] * v[0] + cf[1] * v[1] + cf[2] * v[2] + cf[3] * v[3];
-                        // N_B = 8: the other half of the multivector is in lane ^ 32
-                        if (NB == 8) part += __shfl_xor(part, 32);
-                        v *= gate(part, gle, n / NB);
+                for (int h = 0; h < 2; ++h) {
+                    const int q = 2 * u + h, n = lsp_y_col(S, lane, r, q);
+                    const f4 bb = *reinterpret_cast<const f4*>(ble + n);
+                    f4& v = o[h];
+                    v = f4{acc[r][4 * q], acc[r][4 * q + 1], acc[r][4 * q + 2], acc[r][4 * q + 3]} + bb;
+                    if (has_act) {
+                        const f4 cf = *reinterpret_cast<const f4*>(cle + n);
+                        if constexpr (NB == 2) {
+                            const float g0 = gate(cf[0] * v[0] + cf[1] * v[1], gle, n / 2);
+                            const float g1 = gate(cf[2] * v[2] + cf[3] * v[3], gle, n / 2 + 1);
+                            v[0] *= g0;
+                            v[1] *= g0;
+                            v[2] *= g1;
+                            v[3] *= g1;
+                        } else {
+                            float part = cf[0] * v[0] + cf[1] * v[1] + cf[2] * v[2] + cf[3] * v[3];
+                            // N_B = 8: the other half of the multivector is in lane ^ 32
+                            if (NB == 8) part += __shfl_xor(part, 32);
+                            v *= gate(part, gle, n / NB);
+                        }
                     }
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) z = fmaf(v[e], 0.f, z);
                 }
+                exchange(o[0], o[1]);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) z = fmaf(v[e], 0.f, z);
-              }
-              exchange(o[0], o[1]);
-#pragma unroll
-              for (int h = 0; h < 2; ++h)
-                  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, o[h]), yd,
-                                                         lsp_y_float(S, lane, r, u, h) * 4, 0, 0);
+                for (int h = 0; h < 2; ++h)
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, o[h]), yd,
+                                                           lsp_y_float(S, lane, r, u, h) * 4, 0, 0);
             }
-        if (!more) break;
-        t = tn;
+        return __ballot(z != 0.f) != 0;
+    };
+    {
+        const __amdgpu_buffer_rsrc_t d = x_desc(t0);
+#pragma unroll
+        for (int p = 0; p < PF; ++p) load(d, p, ring[p]);
+    }
+    uint64_t bad = 0;  // bit i % 64: the wave's tile i has an infinite or NaN output
+    int i = 0;
+    for (int64_t t = t0, tn; t < a.n_tile; t = tn, ++i) {
         tn = t + stride;
         tile(t, tn < a.n_tile ? tn : t);
+        bad |= (uint64_t)finish(t) << (i & 63);
     }
-
-    if (__ballot(z != 0.f) == 0) return;
-    // Some outputs of this wave are not finite: its lanes look through them,
-    // one multivector at a time, and compute those again.
-    __threadfence();
-    for (int64_t u = t0; u < a.n_tile; u += stride)
-        for (int e = lane; e < lsp_rows(a, u) * CO; e += 64) {
-            const int64_t row = 32 * u + e / CO;
-            const int co = e % CO;
-            float* const yp = a.y + row * N + co * NB;
-            bool bad = false;
-            for (int i = 0; i < NB; ++i) {
-                const float v = __hip_atomic_load(yp + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                bad = bad || !(fabsf(v) <= 3.4028235e38f);
+    if (bad == 0) return;
+    // Those tiles (and any that share their bit) again as fp32 products on the
+    // fp32 matrix cores, operands straight from memory, one input channel at a
+    // time: values that bf16 parts cannot hold.
+    i = 0;
+    for (int64_t t = t0; t < a.n_tile; t += stride, ++i) {
+        if (!(bad >> (i & 63) & 1)) continue;
+#pragma unroll
+        for (int r = 0; r < RT; ++r)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[r][e] = 0.f;
+        for (int ci = 0; ci < a.C_in; ++ci)
+#pragma unroll
+            for (int h = 0; h < NB / 2; ++h) {
+                const float xv = a.x[lsp_redo_x(S, a, t, lane, ci, h)];
+                const int j = lsp_redo_j(S, lane, h);
+#pragma unroll
+                for (int r = 0; r < RT; ++r) {
+                    const float wv = sign_of(a.sign, (lane & 31) % NB * NB + j) *
+                                     a.w[lsp_redo_w(S, lane, r, ci, h)];
+                    acc[r] = __builtin_amdgcn_mfma_f32_32x32x2f32(wv, xv, acc[r], 0, 0, 0);
+                }
             }
-            if (!bad) continue;
-            float v[NB];
-            for (int i = 0; i < NB; ++i) v[i] = 0.f;
-            for (int ci = 0; ci < a.C_in; ++ci) {
-                const float* xp = a.x + row * K + ci * NB;
-                const float* wp = a.w + lsp_w_float(S, ci, co);
-                for (int i = 0; i < NB; ++i)
-                    for (int j = 0; j < NB; ++j)
-                        v[i] = fmaf(sign_of(a.sign, i * NB + j) * wp[src_blade(NB, i, j)], xp[j], v[i]);
-            }
-            float part = 0.f;
-            for (int i = 0; i < NB; ++i) {
-                v[i] += bl[co * NB + i];
-                part += cl[co * NB + i] * v[i];
-            }
-            const float g = has_act ? gate(part, gl, co) : 1.f;
-            for (int i = 0; i < NB; ++i) yp[i] = has_act ? v[i] * g : v[i];
-        }
+        finish(t);
+    }
 }
 
 template <int NB, int RT, int KQ>

@@ -77,4 +77,24 @@ __host__ __device__ inline int lsp_y_float(const LinSplitShape& S, int lane, int
            4 * (lane >> 5);
 }
 
+// The same product in fp32: the operands of product h (two K slots) of input
+// channel ci.  A lane's slot is blade jb = 2 h + lane / 32 (bitmask); MFMA row
+// lane % 32 of row tile rt is output column n, whose filter blade is src_blade;
+// its X row is lane % 32 of tile t, the batch's last where that lies past it.
+__host__ __device__ inline int lsp_redo_j(const LinSplitShape& S, int lane, int h)
+{
+    return blade_perm(S.NB, 2 * h + (lane >> 5));
+}
+__host__ __device__ inline int lsp_redo_w(const LinSplitShape& S, int lane, int rt, int ci, int h)
+{
+    const int n = 32 * rt + (lane & 31);
+    return lsp_w_float(S, ci, n / S.NB) + src_blade(S.NB, n % S.NB, lsp_redo_j(S, lane, h));
+}
+__host__ __device__ inline int64_t lsp_redo_x(const LinSplitShape& S, const LinSplitArgs& a,
+                                              int64_t t, int lane, int ci, int h)
+{
+    const int64_t row = 32 * t + (lane & 31);
+    return (row < a.B ? row : a.B - 1) * S.K() + ci * S.NB + lsp_redo_j(S, lane, h);
+}
+
 }  // namespace cliff

@@ -119,6 +119,31 @@ void walk(const LaunchPlan& p, const SplitTile& T, const SplitArgs& a)
         // stages: all blocks of small grids, else the first, last and every 61st
         if (sampled && bi > 2 && bi + 3 < a.n_blk && bi % 61) continue;
         current->workgroups++;
+        // the fp32 recompute's reads: each lane's filters, and its positions'
+        // inputs at every tap (the last channel's or position's past the end)
+        for (int wave = 0; wave < T.waves(); ++wave)
+            for (int lane = 0; lane < 64; ++lane) {
+                const int co = std::min(g.co0 + (wave % T.WCO) * T.CW + lane % T.CW, a.C_out - 1);
+                const int64_t w0 = split_redo_w(T, a, g, wave, lane);
+                if (w0 != (int64_t)co * a.taps ||
+                    w0 + ((int64_t)(a.C_in - 1) * a.C_out + 1) * a.taps > n_w) {
+                    fail("recompute reads filter %lld", (long long)w0);
+                    return;
+                }
+                for (int np = 0; np < T.NPT; ++np) {
+                    const int m = std::min(split_out_m(T, g, wave, lane, np), g.m_end - 1);
+                    const int64_t x0 = g.base + split_redo_x<KD>(T, a, g, wave, lane, np);
+                    for (int rt = 0; rt < a.nrt; ++rt)
+                        for (int qx = 0; qx < a.df; ++qx) {
+                            const int64_t x = x0 + split_rt_off<KD>(a, rt) + qx;
+                            if (x != want_x(m, rt, qx) || x < 0 || x + (a.C_in - 1) * img >= n_x) {
+                                fail("recompute reads input %lld of %lld (m %d rt %d qx %d)",
+                                     (long long)x, (long long)n_x, m, rt, qx);
+                                return;
+                            }
+                        }
+                }
+            }
         std::vector<int64_t> groups = {0};
         if (n_grp > 1) groups.push_back(n_grp - 1);
         for (int64_t gi : groups) {

@@ -66,6 +66,22 @@ void check_linear_split(const LaunchPlan& p)
                     return;
                 }
             }
+    // the fp32 recompute's weight reads: product h of input channel ci puts blade
+    // 2 h + lane / 32 into K slot lane / 32
+    for (int lane = 0; lane < 64; ++lane)
+        for (int r = 0; r < S.RT; ++r)
+            for (int ci = 0; ci < a.C_in; ++ci)
+                for (int h = 0; h < S.NB / 2; ++h) {
+                    const int n = 32 * r + (lane & 31), jb = 2 * h + (lane >> 5);
+                    const int ib = blade_perm(S.NB, n % S.NB);
+                    const int64_t want = ((int64_t)ci * a.C_out + n / S.NB) * S.NB +
+                                         blade_perm(S.NB, ib ^ jb);
+                    if (lsp_redo_w(S, lane, r, ci, h) != want || want >= bw->n ||
+                        lsp_redo_j(S, lane, h) != blade_perm(S.NB, jb)) {
+                        fail("recompute reads weight %d", lsp_redo_w(S, lane, r, ci, h));
+                        return;
+                    }
+                }
     const bool sampled = a.n_tile > (1 << 15);
     if (sampled) current->grid_sampled = true;
     std::vector<uint8_t> seen((size_t)N * 32);
@@ -78,6 +94,16 @@ void check_linear_split(const LaunchPlan& p)
         }
         std::fill(seen.begin(), seen.end(), 0);
         for (int lane = 0; lane < 64; ++lane) {
+            for (int ci = 0; ci < a.C_in; ++ci)
+                for (int h = 0; h < S.NB / 2; ++h) {
+                    const int64_t row = std::min<int64_t>(32 * t + (lane & 31), a.B - 1);
+                    const int64_t want =
+                        row * K + ci * S.NB + blade_perm(S.NB, 2 * h + (lane >> 5));
+                    if (lsp_redo_x(S, a, t, lane, ci, h) != want || want < 0 || want >= bx->n) {
+                        fail("recompute reads input %lld", (long long)want);
+                        return;
+                    }
+                }
             // (the kernel adds 64 s + 16 rows h to its first offset)
             for (int s = 0; s < S.KQ; ++s)
                 for (int h = 0; h < 2; ++h) {

@@ -104,6 +104,22 @@ def test_conv_split(case):
     assert e <= 3 * ez
 
 
+def test_conv_split_non_finite_filters():
+    # every blade of some filter infinite or NaN, also where the table's sign
+    # is zero: the classes of the vector kernel
+    for g, shape in (((-1, 0), (1, 8, 64, 300, 3)), ((0, 0, 1), (64, 7, 60, 10, 3)),
+                     ((1, -1), (10, 13, 61, 93, 3))):
+        k = len(g)
+        x, f, _, _ = _inputs(g, shape, None, False, 79)
+        for i in range(1 << k):
+            f[(1, 3 * i) + (1,) * k + (i,)] = np.inf if i % 2 else np.nan
+        y = _run(g, x, f, None, None, P.ALGO_AUTO)
+        r = _run(g, x, f, None, None, P.ALGO_DIRECT)
+        assert np.isnan(r).any() and np.isinf(r).any() and np.isfinite(r).any()
+        np.testing.assert_array_equal(np.isnan(y), np.isnan(r))
+        np.testing.assert_array_equal(y[np.isinf(r)], r[np.isinf(r)])
+
+
 @pytest.mark.parametrize("g,shape", [
     ((1, 1), (1, 8, 64, 300, 3)), ((-1, 0), (1, 8, 64, 300, 3)), ((1, 1, 1), (2, 16, 32, 26, 3)),
     ((1, -1, 1), (2, 16, 32, 26, 3)), ((1, 1), (4, 8, 16, 300, 3)), ((-1, 0), (4, 8, 16, 300, 3)),
@@ -186,3 +202,48 @@ def test_conv_split_blades_of_different_size(g, shape, even):
     n_acc = 6 * -(-shape[1] * nb // 16) * shape[4] ** k
     assert (e <= n_acc * 2.0 ** -23 * size).all()
     assert (e <= 3 * ez).all()
+
+
+def _time(run, reps):
+    run()
+    best = 1e9
+    for _ in range(3):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(reps):
+            run()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b) / reps)
+    return best
+
+
+@pytest.mark.parametrize("g,shape", [
+    ((1, 1), (8, 64, 64, 128, 3)), ((-1, 0), (4, 13, 16, 258, 3)), ((-1,), (1024, 64, 64, 60, 17)),
+    ((1, 1, 1), (2, 32, 32, 32, 3))], ids=str)
+def test_conv_split_masked_channel(g, shape):
+    # an input channel of the lowest value in all images but one: every output of
+    # those is computed again in fp32.  The outputs are the fp32 kernel's
+    # but for the order of the sums (filters of that channel are zero for the
+    # even output channels, which stay of the usual size), and the layer takes no
+    # more than the kernel's own time and twice the fp32 kernel's.
+    k = len(g)
+    x, f, b, _ = _inputs(g, shape, None, True, 78)
+    y0 = _run(g, x, f, b, None, P.ALGO_AUTO)
+    x[1:, 1] = -3.4028235e38
+    f[1, ::2] = 0.0
+    y = _run(g, x, f, b, None, P.ALGO_AUTO)
+    z = _run(g, x, f, b, None, P.ALGO_MFMA)
+    fin = np.isfinite(z)
+    np.testing.assert_array_equal(np.isfinite(y), fin)
+    even = np.zeros_like(fin)
+    even[:, ::2] = True
+    assert fin[even].all() and np.isfinite(y0).all()
+    n = shape[1] * (1 << k) * shape[4] ** k
+    assert np.max(np.abs(y[even] - z[even])) <= 2.0 ** -22 * np.sqrt(n) * np.max(np.abs(z[even]))
+    xt, ft, bt, x0 = dev(x), dev(f), dev(b), dev(np.zeros_like(x))
+    out = torch.empty(y.shape, device="cuda:0")
+    ms = [_time(lambda: P.conv_nd(v, ft, bt, g, out=out, algo=algo), 5)
+          for v, algo in ((xt, P.ALGO_AUTO), (x0, P.ALGO_AUTO), (xt, P.ALGO_MFMA))]
+    print("masked, plain, fp32 kernel: %.3f %.3f %.3f ms" % tuple(ms), flush=True)
+    assert ms[0] <= ms[1] + 2 * ms[2]

@@ -110,3 +110,35 @@ def test_linear_split_non_finite(case):
     np.testing.assert_array_equal(y[np.isinf(r)], r[np.isinf(r)])
     ok = np.isfinite(r) & (np.abs(r) < 1e3)
     assert np.max(np.abs(y[ok] - r[ok])) <= 1e-5 * np.max(np.abs(r[ok]))
+
+
+@pytest.mark.parametrize("case", [((1, 1), 8 * B0 + 7, 32, 32, (LIN, (0, 2)), True),
+                                  ((-1,), 8 * B0, 64, 32, None, False),
+                                  ((0, -1, 1), 8 * B0 + 40, 16, 16, None, True)], ids=str)
+def test_linear_split_masked_channel(case):
+    # an input channel of the lowest value in all rows but 32: those are
+    # computed again in fp32.  The outputs are the fp32 kernel's but for the
+    # order of the sums (the channel's weights are zero for the even output
+    # channels), in no more than the kernel's own time and the fp32 kernel's
+    # twice.
+    from test_conv_split_gpu import _time
+    g, B, C_in, C_out = case[:4]
+    x, w, b, act = _inputs(*case, seed=6)
+    x0 = x.copy()
+    x[32:, 1] = -3.4028235e38
+    w[1, ::2] = 0.0
+    y = _run(g, x, w, b, act)
+    z = _run(g, x, w, b, act, P.ALGO_MFMA_STREAM)
+    np.testing.assert_array_equal(np.isfinite(y), np.isfinite(z))
+    assert np.isfinite(z[:, ::2]).all()
+    assert np.max(np.abs(y[:, ::2] - z[:, ::2])) <= \
+        2.0 ** -22 * np.sqrt(C_in * x.shape[-1]) * np.max(np.abs(z[:, ::2]))
+    a = None if act is None else tuple(v if i < 2 or v is None else dev(v) for i, v in enumerate(act))
+    wt, bt, out = dev(w), None if b is None else dev(b), torch.empty(y.shape, device="cuda:0")
+    k, nb = len(g), x.shape[-1]
+    one = (1,) * k + (nb,)
+    ms = [_time(lambda: P.conv_nd(v.reshape(v.shape[:2] + one), wt.reshape(w.shape[:2] + one), bt, g,
+                                  act=a, out=out.reshape(out.shape[:2] + one), algo=algo), 10)
+          for v, algo in ((dev(x), P.ALGO_AUTO), (dev(x0), P.ALGO_AUTO), (dev(x), P.ALGO_MFMA_STREAM))]
+    print("masked, plain, fp32 kernel: %.3f %.3f %.3f ms" % tuple(ms), flush=True)
+    assert ms[0] <= ms[1] + 2 * ms[2]
