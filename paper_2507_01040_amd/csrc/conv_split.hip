@@ -4,8 +4,9 @@
 // v_mfma_f32_32x32x16_bf16.
 //
 // Parts.  h = bf16(v), m = bf16(v - h), l = bf16(v - h - m), rounded to
-// nearest: v = h + m + l to the last bit.  The products h h, h m, m h, m m,
-// h l, l h are kept; those left out are below 2^-24 of the operands' product.
+// nearest, of v = 2^16 times the operand (split.hpp): v = h + m + l to the last
+// bit, for every float below 2^112.  The products h h, h m, m h, m m, h l, l h
+// are kept; those left out are below 2^-24 of the operands' product.
 //
 // Row i of an MFMA tile's rows is output blade i, and the K slots of an input
 // channel are its blades j with filter blade i ^ j and the table's sign, so
@@ -50,8 +51,8 @@
 // instead of at the start of a step (360 -> 397 us), all taps of a row loaded at
 // once (360 -> 369 us).
 //
-// Values that bf16 arithmetic cannot carry (infinities, the largest floats, sums
-// past them) come out non-finite; a wave that holds such a sum computes all of
+// Values that bf16 arithmetic cannot carry (infinities, operands from 2^112 and
+// sums from 2^96 on) come out non-finite; a wave that holds such a sum computes all of
 // its sums again on the fp32 matrix cores (split_fp32_sums).  With a channel of
 // the lowest value in 7 of 8 images C 64, d 128 takes 1.79 ms (fp32 tiles 1.08;
 // with half of the images masked and one lane for an output 16.3 ms), k = 1,
@@ -468,8 +469,7 @@ __global__ __launch_bounds__(64 * WCO * WPOS, 2) void conv_split_kernel(SplitArg
         cur = nst;
     }
 
-    // Infinite or NaN sums (parts of infinities and of the largest floats, sums
-    // past them): every row of a multivector is in this wave, so a filter blade
+    // Infinite or NaN sums (of infinities, operands from 2^112, sums from 2^96): every row of a multivector is in this wave, so a filter blade
     // dropped with its zero sign shows in the row where its sign is not zero.
     float z = 0.f;
 #pragma unroll
@@ -478,7 +478,11 @@ __global__ __launch_bounds__(64 * WCO * WPOS, 2) void conv_split_kernel(SplitArg
         for (int n = 0; n < NPT; ++n)
 #pragma unroll
             for (int e = 0; e < 16; ++e) z = fmaf(acc[r][n][e], 0.f, z);
-    if (__ballot(z != 0.f)) split_fp32_sums<KD, NB>(T, a, g, wave, lane, acc);
+    float unscale = SPLIT_UNSCALE;
+    if (__ballot(z != 0.f)) {
+        split_fp32_sums<KD, NB>(T, a, g, wave, lane, acc);
+        unscale = 1.f;
+    }
 
     // Epilogue: bias, optional activation; one lane holds a whole multivector.
     const bool has_act = a.act.mode >= 0;
@@ -498,7 +502,7 @@ __global__ __launch_bounds__(64 * WCO * WPOS, 2) void conv_split_kernel(SplitArg
             if (m >= g.m_end || co >= a.C_out) continue;
             float v[NB];
 #pragma unroll
-            for (int i = 0; i < NB; ++i) v[blade_perm(NB, i)] = el(i, np, e);
+            for (int i = 0; i < NB; ++i) v[blade_perm(NB, i)] = el(i, np, e) * unscale;
             if (a.bias) {
 #pragma unroll
                 for (int i = 0; i < NB; ++i) v[i] += a.bias[co * NB + i];

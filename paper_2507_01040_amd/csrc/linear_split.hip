@@ -23,8 +23,8 @@
 // of 4: 242.  64 -> 256 columns spill (8 row tiles) and stay there, as do
 // 64 -> 64, at the memory's rate already, and 256 -> 256.
 //
-// Tiles with a result that is not finite (bf16 parts cannot hold infinities) are
-// computed again on the fp32 matrix cores after the wave's last one: with a
+// Tiles with a result that is not finite (infinities, operands from 2^112 and sums
+// from 2^96 on) are computed again on the fp32 matrix cores after the wave's last one: with a
 // channel of the lowest value in all rows 2^17 rows of 32 -> 32 channels take 96
 // us instead of 38 (half of 2^18 rows, one lane for an output: 437 us).
 #include <stdio.h>
@@ -187,9 +187,9 @@ __global__ __launch_bounds__(512, 2) void linear_split_kernel(LinSplitArgs a)
         if (mean) s = s / (float)a.act.K;
         return 1.0f / (1.0f + __expf(-s));
     };
-    // Tile t's outputs from the accumulators; whether one of them is infinite or
-    // NaN (in any lane).
-    auto finish = [&](int64_t t) {
+    // Tile t's outputs from the accumulators, which hold 1 / unscale times its
+    // sums; whether one of them is infinite or NaN (in any lane).
+    auto finish = [&](int64_t t, float unscale) {
         float z = 0.f;
         const __amdgpu_buffer_rsrc_t yd = __builtin_amdgcn_make_buffer_rsrc(
             a.y + 32 * t * N, (short)0, lsp_rows(a, t) * N * 4, 0x00020000);
@@ -210,7 +210,8 @@ __global__ __launch_bounds__(512, 2) void linear_split_kernel(LinSplitArgs a)
                     const int q = 2 * u + h, n = lsp_y_col(S, lane, r, q);
                     const f4 bb = *reinterpret_cast<const f4*>(ble + n);
                     f4& v = o[h];
-                    v = f4{acc[r][4 * q], acc[r][4 * q + 1], acc[r][4 * q + 2], acc[r][4 * q + 3]} + bb;
+                    v = f4{acc[r][4 * q], acc[r][4 * q + 1], acc[r][4 * q + 2], acc[r][4 * q + 3]} * unscale +
+                        bb;
                     if (has_act) {
                         const f4 cf = *reinterpret_cast<const f4*>(cle + n);
                         if constexpr (NB == 2) {
@@ -248,7 +249,7 @@ __global__ __launch_bounds__(512, 2) void linear_split_kernel(LinSplitArgs a)
     for (int64_t t = t0, tn; t < a.n_tile; t = tn, ++i) {
         tn = t + stride;
         tile(t, tn < a.n_tile ? tn : t);
-        bad |= (uint64_t)finish(t) << (i & 63);
+        bad |= (uint64_t)finish(t, SPLIT_UNSCALE) << (i & 63);
     }
     if (bad == 0) return;
     // Those tiles (and any that share their bit) again as fp32 products on the
@@ -273,7 +274,7 @@ __global__ __launch_bounds__(512, 2) void linear_split_kernel(LinSplitArgs a)
                     acc[r] = __builtin_amdgcn_mfma_f32_32x32x2f32(wv, xv, acc[r], 0, 0, 0);
                 }
             }
-        finish(t);
+        finish(t, 1.f);
     }
 }
 

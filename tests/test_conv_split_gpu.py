@@ -247,3 +247,26 @@ def test_conv_split_masked_channel(g, shape):
           for v, algo in ((xt, P.ALGO_AUTO), (x0, P.ALGO_AUTO), (xt, P.ALGO_MFMA))]
     print("masked, plain, fp32 kernel: %.3f %.3f %.3f ms" % tuple(ms), flush=True)
     assert ms[0] <= ms[1] + 2 * ms[2]
+
+
+@pytest.mark.parametrize("ex,ew", [(-118, 0), (-124, 0), (0, -118), (-60, -60), (-140, 20), (60, 40),
+                                   (100, -20), (0, 110)], ids=str)
+@pytest.mark.parametrize("g,shape", [((-1, -1), (1, 24, 64, 128, 3)), ((-1,), (2000, 21, 62, 61, 17)),
+                                     ((1, 1, 1), (2, 16, 32, 26, 3))], ids=str)
+def test_conv_split_operand_range(g, shape, ex, ew):
+    # operands times powers of two, from where the low parts of bf16 run out
+    # (subnormal inputs and sums past 2^96 among them): the tolerance of
+    # test_conv_split; inputs below 2^-126 keep the bits that they have
+    print(g, shape, ex, ew, flush=True)
+    x, f, _, _ = _inputs(g, shape, None, False, 80)
+    x, f = np.ldexp(x, ex), np.ldexp(f, ew)
+    y = _run(g, x, f, None, None, P.ALGO_AUTO)
+    sel = sorted({0, shape[0] - 1})
+    xs, fs = np.ldexp(x[sel].astype(np.float64), -ex), np.ldexp(f.astype(np.float64), -ew)
+    assert (xs.astype(np.float32) == xs).all() and (fs.astype(np.float32) == fs).all()
+    ref = oracle.conv_nd(xs.astype(np.float32), fs.astype(np.float32),
+                         np.zeros((shape[2], 1 << len(g)), np.float32), g)
+    n = shape[1] * (1 << len(g)) * shape[4] ** len(g)
+    e = normwise(np.ldexp(y[sel].astype(np.float64), -ex - ew), ref)
+    print("normwise %.2e" % e, flush=True)
+    assert e <= 2.0 ** -23 * np.sqrt(n)

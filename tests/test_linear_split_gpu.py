@@ -142,3 +142,18 @@ def test_linear_split_masked_channel(case):
           for v, algo in ((dev(x), P.ALGO_AUTO), (dev(x0), P.ALGO_AUTO), (dev(x), P.ALGO_MFMA_STREAM))]
     print("masked, plain, fp32 kernel: %.3f %.3f %.3f ms" % tuple(ms), flush=True)
     assert ms[0] <= ms[1] + 2 * ms[2]
+
+
+@pytest.mark.parametrize("ex,ew", [(-118, 0), (-124, 0), (0, -118), (-140, 20), (60, 40), (0, 110)], ids=str)
+def test_linear_split_operand_range(ex, ew):
+    # as for the convolution
+    g, B, C_in, C_out = (1, 1), 2 * B0 + 17, 32, 32
+    x, w, _, _ = _inputs(g, B, C_in, C_out, None, False, 8)
+    x, w = np.ldexp(x, ex), np.ldexp(w, ew)
+    y = _run(g, x, w, None, None)
+    sel = np.unique(np.r_[0:64, B - 64:B])
+    xs, ws = np.ldexp(x[sel].astype(np.float64), -ex), np.ldexp(w.astype(np.float64), -ew)
+    ref = oracle.linear(xs.astype(np.float32), ws.astype(np.float32), np.zeros((C_out, 4), np.float32), g)
+    e = normwise(np.ldexp(y[sel].astype(np.float64), -ex - ew), ref)
+    print("normwise %.2e" % e, flush=True)
+    assert e <= 2.0 ** -23 * np.sqrt(4 * C_in)
