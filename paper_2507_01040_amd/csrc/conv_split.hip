@@ -681,6 +681,17 @@ cliff_status launch_conv_split(const ConvProblem& p, hipStream_t stream)
 {
     if (launch_observer && launch_observer->last_kind < LAUNCH_CONV_SPLIT) return CLIFF_EUNSUPPORTED;
     if (p.d_filter < 2) return CLIFF_EUNSUPPORTED;
+    // A sum's error goes with its roundings: a tap costs six here for every 16 K
+    // slots, and one on the fp32 tiles for every product that the table does not
+    // make zero.  Tables without zeros: 0.80 to 0.97 of the fp32 tiles' error
+    // (2-norm, all C_in and filters, up to 18816 products).  With zeros it is 0.87
+    // to 0.99 while there are at most 0.56 times as many roundings; past that up to
+    // 1.05 (k = 2, 3, 5 or 7 input channels; k = 3 with two zeros in g).
+    if (p.sign.zero) {
+        const int64_t cpg = 16 / p.nb, nz = p.nb * p.nb - __builtin_popcountll(p.sign.zero);
+        if (6.0 * (double)((p.C_in + cpg - 1) / cpg) > 0.56 * (double)p.C_in * nz / p.nb)
+            return CLIFF_EUNSUPPORTED;
+    }
     // Taken where the estimate is below the time of the fp32 tiles at their
     // best rate (146 TFLOP/s, 0.93 of the fp32 peak, on the largest layers;
     // 141 for k = 1); smaller layers, where that rate is out of reach for

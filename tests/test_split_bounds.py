@@ -31,6 +31,14 @@ def test_parity_cases():
         assert ".".join(t[2:5] + (["16"] if t[6] == "16" else [])) == tile, (g, shape, res)
 
 
+def test_zero_signatures():
+    import test_conv_split_gpu as T
+    lines = [conv_line(len(g), g, *shape, P.ALGO_AUTO) for g, shape, _ in T.ZEROS]
+    for res, (g, shape, kind) in zip(_run(lines), T.ZEROS):
+        f = res.split()
+        assert f[0] == "ok" and f[4] == kind, (g, shape, res)
+
+
 def test_benchmark_layers_and_sizes():
     # the benchmark's convolutions, and layers that stay with the fp32 kernels:
     # small ones, forced tiles, the vector kernel, linear layers
