@@ -692,6 +692,11 @@ cliff_status launch_conv_split(const ConvProblem& p, hipStream_t stream)
         if (6.0 * (double)((p.C_in + cpg - 1) / cpg) > 0.56 * (double)p.C_in * nz / p.nb)
             return CLIFF_EUNSUPPORTED;
     }
+    // One K group with padding channels at four taps or less: the output's stores
+    // are most of the time and hidden by too little (k = 2, 2x2 filters, C_in 3,
+    // 62 channels, B 13, d 324 491 us on the fp32 tiles, 544 here; C_in 4, 63
+    // channels, B 5, d 488 516, 465).
+    if (p.C_in < 16 / p.nb && std::pow((double)p.d_filter, p.k) <= 4) return CLIFF_EUNSUPPORTED;
     // Taken where the estimate is below the time of the fp32 tiles at their
     // best rate (146 TFLOP/s, 0.93 of the fp32 peak, on the largest layers;
     // 141 for k = 1); smaller layers, where that rate is out of reach for

@@ -51,6 +51,11 @@ def test_benchmark_layers_and_sizes():
     for algo, kind in ((P.ALGO_MFMA, "1"), (P.ALGO_MFMA_WIDE, "1"), (P.ALGO_DIRECT, "3")):
         lines.append(conv_line(*big, algo))
         want.append(kind)
+    # few steps: the K group full or not
+    for g, shape, kind in (((-1, -1), (13, 3, 62, 324, 2), "1"), ((1, 1), (8, 3, 64, 406, 2), "1"),
+                           ((-1, -1), (5, 4, 63, 488, 2), "7"), ((1, 1), (8, 3, 64, 258, 3), "7")):
+        lines.append(conv_line(2, g, *shape, P.ALGO_AUTO))
+        want.append(kind)
     for k, g, shape in ((2, (1, 1), (8, 4, 4, 16, 3)), (3, (1, 1, 1), (2, 8, 8, 12, 3)),
                         (2, (1, 1), (1000, 32, 32, 1, 1)), (1, (-1,), (64, 16, 16, 60, 17))):
         lines.append(conv_line(k, g, *shape, P.ALGO_AUTO))
