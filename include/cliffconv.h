@@ -182,9 +182,10 @@ cliff_status clifford_conv_nd_algo(int k, const int8_t* g, int64_t B,
  * the convolution with d_image = d_filter = 1.  Layers with C_in N_B and
  * C_out N_B each 64, 128 or 256 and B >= 16384 run on a streamed kernel that
  * keeps the weight in LDS: on fp32 MFMA (CLIFF_ALGO_MFMA and
- * CLIFF_ALGO_MFMA_STREAM), or, by the automatic choice and for C_in N_B ->
- * C_out N_B = 128 -> 128, 64 -> 128, 128 -> 64 and 256 -> 64, on bf16 MFMA with
- * every fp32 operand as the sum of three bf16 parts.  Other layers run on the
+ * CLIFF_ALGO_MFMA_STREAM), or, by the automatic choice for C_in N_B ->
+ * C_out N_B = 128 -> 64 and 256 -> 64, and from 18432 or 32769 rows on for 128 ->
+ * 128 and 64 -> 128, on bf16 MFMA with every fp32 operand as the sum of three
+ * bf16 parts.  Other layers run on the
  * convolution kernels.
  */
 cliff_status clifford_linear(int k, const int8_t* g, int64_t B, int64_t C_in,

@@ -171,8 +171,7 @@ ActParams to_params(const cliff_act_desc* act)
 // Linear layers: the streamed kernels from 16384 rows on (measured on MI355X
 // over 7 widths: from there the fp32 one beats every convolution tile; below,
 // the tiny and medium tiles are 1-4 us faster).  The split one goes first where
-// it has the width (16384 rows of 32 -> 32 channels: 15.2 -> 14.5 us; its
-// workgroups each expand the weight first), for the automatic choice only.
+// it has the width and the rows, for the automatic choice only.
 bool linear_stream_pays(const ConvProblem& p)
 {
     return p.B >= 16 * 1024;

@@ -327,6 +327,16 @@ cliff_status launch_linear_split(const ConvProblem& p, hipStream_t stream)
     if (launch_observer && launch_observer->last_kind < LAUNCH_LINEAR_SPLIT)
         return CLIFF_EUNSUPPORTED;
     if (p.d_image != 1 || p.d_filter != 1) return CLIFF_EUNSUPPORTED;
+    // Rows from which it is ahead of the fp32 streamed kernel, which fills its
+    // first round of waves at 32768 rows.  Every workgroup expands the weight first:
+    // 128 columns of k = 3, and 64 -> 128, lose until then (32768 rows of 16 -> 16
+    // channels, k = 3: 17.0 us, fp32 15.5; 40000: 17.3, 24.1; k = 2, 16 -> 32:
+    // 12.5, 12.1; 40000: 12.4, 17.4), 128 -> 128 of k = 1 and 2 until about 18000
+    // (k = 2: 16384 rows 14.9, 14.6; 20480: 15.0, 15.4); 64 columns are ahead
+    // from 16384 on (k = 2, 128 -> 64: 11.6, 15.4).
+    const bool wide = p.C_out * p.nb == 128;
+    const int64_t rows = !wide ? 16384 : p.nb == 8 || p.C_in * p.nb == 64 ? 32769 : 18432;
+    if (p.B < rows) return CLIFF_EUNSUPPORTED;
     switch (p.nb) {
         case 2: return run_nk<2>(p, stream);
         case 4: return run_nk<4>(p, stream);

@@ -18,12 +18,12 @@ from gpu_util import dev, normwise
 pytestmark = pytest.mark.gpu
 
 LIN, SUM, MEAN = P.AGG_LINEAR, P.AGG_SUM, P.AGG_MEAN
-B0 = 16384
+B0 = 32768
 # (g, B, C_in, C_out, gate or None, bias)
 CASES = [
     ((1, 1), B0 + 17, 32, 32, None, True),
     ((-1, 0), B0 + 31, 32, 32, (LIN, (0, 1, 2, 3)), True),
-    ((1, -1), 5 * B0 + 1, 16, 32, (SUM, (2, 1)), False),
+    ((1, -1), 3 * B0 + 1, 16, 32, (SUM, (2, 1)), False),
     ((1, 1), B0, 32, 16, (MEAN, (3,)), True),
     ((0, 1), B0 + 1, 64, 16, None, False),
     ((-1,), B0 + 33, 64, 64, (LIN, (1, 0)), True),
@@ -112,9 +112,9 @@ def test_linear_split_non_finite(case):
     assert np.max(np.abs(y[ok] - r[ok])) <= 1e-5 * np.max(np.abs(r[ok]))
 
 
-@pytest.mark.parametrize("case", [((1, 1), 8 * B0 + 7, 32, 32, (LIN, (0, 2)), True),
-                                  ((-1,), 8 * B0, 64, 32, None, False),
-                                  ((0, -1, 1), 8 * B0 + 40, 16, 16, None, True)], ids=str)
+@pytest.mark.parametrize("case", [((1, 1), 4 * B0 + 7, 32, 32, (LIN, (0, 2)), True),
+                                  ((-1,), 4 * B0, 64, 32, None, False),
+                                  ((0, -1, 1), 4 * B0 + 40, 16, 16, None, True)], ids=str)
 def test_linear_split_masked_channel(case):
     # an input channel of the lowest value in all rows but 32: those are
     # computed again in fp32.  The outputs are the fp32 kernel's but for the
@@ -147,7 +147,7 @@ def test_linear_split_masked_channel(case):
 @pytest.mark.parametrize("ex,ew", [(-118, 0), (-124, 0), (0, -118), (-140, 20), (60, 40), (0, 110)], ids=str)
 def test_linear_split_operand_range(ex, ew):
     # as for the convolution
-    g, B, C_in, C_out = (1, 1), 2 * B0 + 17, 32, 32
+    g, B, C_in, C_out = (1, 1), B0 + 17, 32, 32
     x, w, _, _ = _inputs(g, B, C_in, C_out, None, False, 8)
     x, w = np.ldexp(x, ex), np.ldexp(w, ew)
     y = _run(g, x, w, None, None)

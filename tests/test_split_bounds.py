@@ -80,7 +80,12 @@ def test_linear_layers():
     S = P.ALGO_MFMA_STREAM
     cases = [(g, B, ci, co, gate, "8", "4", "4") for g, B, ci, co, gate, _ in T.CASES]
     cases += [((1, 1), 1 << 20, 32, 32, None, "8", "4", "4"),
-              ((1, 1), T.B0 - 1, 32, 32, None, "1", "1", "4"),
+              ((1, 1), 16383, 32, 32, None, "1", "1", "4"),
+              ((1, 1), 18431, 32, 32, None, "4", "4", "4"),
+              ((1, 1), 18432, 32, 32, None, "8", "4", "4"),
+              ((1, 1, 1), 32768, 16, 16, None, "4", "4", "4"),
+              ((-1,), 32768, 32, 64, None, "4", "4", "4"),
+              ((-1,), 16384, 64, 32, None, "8", "4", "4"),
               ((1,), 1 << 21, 32, 32, None, "4", "4", "4"),
               ((1, 1), 1 << 18, 24, 32, None, "1", "1", None)]
     lines, want = [], []
