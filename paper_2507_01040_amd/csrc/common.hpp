@@ -115,7 +115,7 @@ struct LaunchObserver {
     int cus;  // compute units the dispatch heuristics assume
     void (*on_launch)(const LaunchPlan& plan, void* ctx);
     void* ctx;
-    int last_kind = LAUNCH_ACT;  // the kinds it can walk; other kernels are not chosen
+    int last_kind = LAUNCH_LINEAR_SPLIT;  // the kinds it can walk; other kernels are not chosen
 };
 extern LaunchObserver* launch_observer;
 
@@ -144,7 +144,7 @@ cliff_status launch_conv_direct(const ConvProblem& p, hipStream_t stream);
 cliff_status launch_conv_mfma(const ConvProblem& p, hipStream_t stream);
 // k = 1 on the matrix cores; CLIFF_EUNSUPPORTED without launching likewise.
 cliff_status launch_conv1d_mfma(const ConvProblem& p, hipStream_t stream);
-// k = 2, 3 on the bf16 matrix cores with split operands; likewise.
+// k = 1, 2, 3 on the bf16 matrix cores with split operands; likewise.
 cliff_status launch_conv_split(const ConvProblem& p, hipStream_t stream);
 // Linear layers (d_image = d_filter = 1) on the streamed MFMA kernel;
 // CLIFF_EUNSUPPORTED without launching when the channel counts do not fit it.

@@ -604,7 +604,7 @@ cliff_status run(const ConvProblem& p, hipStream_t stream, int64_t* blocks)
                 "%lld workgroups of %d, %d LDS bytes\n",
                 KD, (int)df, T.co_wg(), (int)P, (long long)n_blk,
                 T.nt(), T.lds_bytes());
-    if (observe_launch(LAUNCH_CONV_SPLIT, {KD, NB, WCO, WPOS, NPT, LP, CW}, n_blk, T.nt(),
+    if (observe_launch(LAUNCH_CONV_SPLIT, {KD, NB, DF, WCO, WPOS, NPT, LP, CW}, n_blk, T.nt(),
                        T.lds_bytes(), &a))
         return CLIFF_OK;
     clear_hip_error();

@@ -50,7 +50,8 @@ void walk(const LaunchPlan& p, const SplitTile& T, const SplitArgs& a)
         return;
     }
     const int64_t n_grp = (a.C_in + T.cpg() - 1) / T.cpg();
-    if (a.nx > split_rounds(KD, 0) || a.xi > 2 || (int64_t)a.xi * a.df < a.nx || a.n_step != n_grp * a.taps ||
+    const int DF = p.tpl[2];
+    if ((DF && DF != a.df) || a.nx > split_rounds(KD, DF) || a.xi > (DF ? 1 : 2) || (int64_t)a.xi * a.df < a.nx || a.n_step != n_grp * a.taps ||
         a.nrt * a.df != a.taps || a.nrow * a.Do != a.M || (bb && bb->n < (int64_t)a.C_out * NB)) {
         fail("stage plan: nx %d xi %d n_step %d", a.nx, a.xi, a.n_step);
         return;
@@ -269,7 +270,8 @@ void walk(const LaunchPlan& p, const SplitTile& T, const SplitArgs& a)
 void check_conv_split(const LaunchPlan& p)
 {
     const SplitArgs& a = *static_cast<const SplitArgs*>(p.args);
-    const SplitTile T{p.tpl[0], p.tpl[1], p.tpl[2], p.tpl[3], p.tpl[4], p.tpl[5], p.tpl[6]};
+    // tpl[2]: the unrolled filter length, 0 for any
+    const SplitTile T{p.tpl[0], p.tpl[1], p.tpl[3], p.tpl[4], p.tpl[5], p.tpl[6], p.tpl[7]};
     if (T.KD == 1) walk<1>(p, T, a);
     if (T.KD == 2) walk<2>(p, T, a);
     if (T.KD == 3) walk<3>(p, T, a);

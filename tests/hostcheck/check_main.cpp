@@ -18,7 +18,7 @@
 //   conv   k g_1..g_k B C_in C_out d_image d_filter algo  ACT
 //   block  k g_1..g_k B C_in C_mid C_out d_image d_filter path  ACT ACT
 //   act    nb B C P  ACT
-//   kinds  n  (the highest LaunchKind the cases after it may launch)
+//   kinds  n  (the highest LaunchKind the cases after it may launch; all without)
 //   fastdiv  (the reciprocal division of the kernels' index arithmetic)
 // with ACT = mode K blade_1..blade_K (mode -1: none, K then 0).
 // Output: one line per case, "ok <status> <launches> <simulated workgroups>

@@ -27,11 +27,12 @@ def _entries(B):
 
 
 @pytest.mark.parametrize("B,C_in,C_out,d,algo,act", [
-    (1024, 64, 64, 60, P.ALGO_AUTO, False),
+    (1024, 64, 64, 60, P.ALGO_AUTO, False),        # the split kernel
+    (1024, 64, 64, 60, P.ALGO_MFMA, False),
     (1000, 64, 62, 60, P.ALGO_MFMA_WIDE, False),   # C_out below the tile's 64 channels
-    (1001, 64, 64, 61, P.ALGO_AUTO, True),         # odd d_image: 4-byte input loads
-    (2048, 128, 128, 60, P.ALGO_AUTO, True),       # two channel blocks
-], ids=["B1024-C64", "B1000-C62-wide", "B1001-d61-act", "B2048-C128-act"])
+    (1001, 64, 64, 61, P.ALGO_MFMA, True),         # odd d_image: 4-byte input loads
+    (2048, 128, 128, 60, P.ALGO_MFMA, True),       # two channel blocks
+], ids=["B1024-C64", "B1024-C64-fp32", "B1000-C62-wide", "B1001-d61-act", "B2048-C128-act"])
 def test_conv1d_176(B, C_in, C_out, d, algo, act):
     g = (-1,)
     df = 17

@@ -17,7 +17,9 @@ standalone activation (check_act.cpp) and the direct (vector-ALU) kernel
 
 Cases: the GPU parity shapes with every tile shape forced, the benchmark's
 workloads at full size, the random sweeps' draws (convolutions and blocks),
-the block entry point's cases, and wide images.  Each must come back "ok"
+the block entry point's cases, and wide images.  The tests of one fp32 tile take
+CLIFF_ALGO_MFMA, its choice among the fp32 tiles: CLIFF_ALGO_AUTO gives larger
+layers to the split kernels (tests/test_split_bounds.py).  Each must come back "ok"
 with the status the GPU tests expect (CLIFF_OK, or CLIFF_EUNSUPPORTED for a
 forced tile that refuses a shape).
 """
@@ -180,7 +182,7 @@ def test_conv1d_176_position_tile():
                                   (1000, 64, 62, 60, 11), (2048, 128, 128, 60, 11),
                                   (1001, 64, 64, 61, 11), (8192, 64, 64, 60, 4),
                                   (1000, 64, 63, 60, 4)):
-        for algo in (P.ALGO_AUTO, P.ALGO_MFMA_WIDE):
+        for algo in (P.ALGO_MFMA, P.ALGO_MFMA_WIDE):
             cases.append(("1-D B %d C %d->%d d %d algo %s" % (B, C_in, C_out, d, ALGO_NAMES[algo]),
                           conv_line(1, (-1,), B, C_in, C_out, d, 17, algo)))
             want.append(nw)
@@ -205,7 +207,7 @@ def test_wide_112_position_tiles():
                                         (3, (1, -1, 1), 8, 32, 32, 36, 7), (3, (1, 1, 1), 8, 32, 32, 42, 7),
                                         (3, (1, 1, 1), 8, 32, 32, 32, 6), (3, (1, 1, 1), 8, 32, 32, 34, 8)):
         cases.append(("%dD B %d C %d->%d d %d" % (k, B, C_in, C_out, d),
-                      conv_line(k, g, B, C_in, C_out, d, 3, P.ALGO_AUTO)))
+                      conv_line(k, g, B, C_in, C_out, d, 3, P.ALGO_MFMA)))
         want.append(nw)
     out = _run_cases(cases, lambda line: False)
     for (label, _), res, nw in zip(cases, out, want):
@@ -221,12 +223,12 @@ def test_wide_16_channel_tile():
     import test_parity_gpu as T
     cases = []
     for g, (B, C_in, C_out, d, df) in T.WIDE16_CASES:
-        for algo in (P.ALGO_MFMA_WIDE, P.ALGO_AUTO):
+        for algo in (P.ALGO_MFMA_WIDE, P.ALGO_MFMA):
             cases.append(("%s %s algo %s" % (g, (B, C_in, C_out, d, df), ALGO_NAMES[algo]),
                           conv_line(2, g, B, C_in, C_out, d, df, algo)))
     for B, C, d in ((2, 16, 2050), (1, 12, 4098), (128, 16, 130)):
         cases.append(("2D B %d C %d d %d auto" % (B, C, d),
-                      conv_line(2, (1, 1), B, C, C, d, 3, P.ALGO_AUTO)))
+                      conv_line(2, (1, 1), B, C, C, d, 3, P.ALGO_MFMA)))
     out = _run_cases(cases, lambda line: False)
     for (label, _), res in zip(cases, out):
         f = res.split()
@@ -241,7 +243,7 @@ def test_small_channel_tile_widths():
     # the automatic choice among the 16- and 8-channel tiles' widths (512,
     # 384 or 256 positions; template WCO.WPOS.MW.NW) on the GPU parity cases
     import test_parity_gpu as T
-    cases = [("%s %s" % (g, shape), conv_line(2, g, *shape, P.ALGO_AUTO))
+    cases = [("%s %s" % (g, shape), conv_line(2, g, *shape, P.ALGO_MFMA))
              for g, shape in T.SMALL_CHANNEL_WIDTH_CASES]
     out = _run_cases(cases, lambda line: False)
     for (label, _), res, want in zip(cases, out, T.SMALL_CHANNEL_WIDTH_TILES):
@@ -256,7 +258,7 @@ def test_3d_8_channel_tile():
     import test_parity_gpu as T
     cases = []
     for g, shape in T.W3_8_CASES + [((1, 1, 1), (8, 8, 8, 34, 3)), ((1, 0, 1), (2, 8, 8, 66, 3))]:
-        for algo in (P.ALGO_MFMA_WIDE, P.ALGO_AUTO):
+        for algo in (P.ALGO_MFMA_WIDE, P.ALGO_MFMA):
             cases.append(("%s %s %s" % (g, shape, ALGO_NAMES[algo]),
                           conv_line(3, g, *shape, algo)))
     out = _run_cases(cases, lambda line: False)
@@ -280,7 +282,7 @@ def test_5x5_7x7_unrolled():
                             ((1, 1), (2, 64, 64, 262, 7)), ((1, 1), (32, 8, 8, 134, 7))]
     dfs = []
     for g, shape in shapes:
-        for algo in (P.ALGO_AUTO, P.ALGO_MFMA_WIDE, P.ALGO_MFMA_MEDIUM, P.ALGO_MFMA_NARROW,
+        for algo in (P.ALGO_MFMA, P.ALGO_MFMA_WIDE, P.ALGO_MFMA_MEDIUM, P.ALGO_MFMA_NARROW,
                      P.ALGO_MFMA_TINY):
             cases.append(("%s %s %s" % (g, shape, ALGO_NAMES[algo]),
                           conv_line(2, g, *shape, algo)))
@@ -298,7 +300,7 @@ def test_narrow_10_slots():
     import test_parity_gpu as T
     cases = []
     for g, shape in T.NARROW10_CASES + [((1, 1), (8, 64, 64, 130, 7)), ((1, 1), (2, 64, 64, 262, 7))]:
-        for algo in (P.ALGO_AUTO, P.ALGO_MFMA_NARROW):
+        for algo in (P.ALGO_MFMA, P.ALGO_MFMA_NARROW):
             cases.append(("%s %s %s" % (g, shape, ALGO_NAMES[algo]),
                           conv_line(2, g, *shape, algo)))
     out = _run_cases(cases, lambda line: False)
@@ -313,7 +315,7 @@ def test_wide_64_position_tile():
     # WCO.WPOS.MW.NW 4.1.4.4), which the automatic choice takes for small
     # single-image layers
     import test_parity_gpu as T
-    cases = [("%s %s" % (g, shape), conv_line(2, g, *shape, P.ALGO_AUTO))
+    cases = [("%s %s" % (g, shape), conv_line(2, g, *shape, P.ALGO_MFMA))
              for g, shape in T.WIDE64_CASES + [((1, 1), (1, 64, 64, 128, 3))]]
     out = _run_cases(cases, lambda line: False)
     for (label, _), res in zip(cases, out):

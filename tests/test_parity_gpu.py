@@ -331,7 +331,7 @@ def test_wide_tile_fallbacks(shape):
     g = (1, 1)
     s, x, f, b = _case(130 + shape[3], g, shape)
     ref = oracle.conv_nd(x, f, b, g)
-    for algo in (P.ALGO_AUTO, P.ALGO_MFMA_WIDE):
+    for algo in (P.ALGO_AUTO, P.ALGO_MFMA, P.ALGO_MFMA_WIDE):
         assert_parity(gpu_conv(g, x, f, b, algo=algo), ref, what="algo %d" % algo)
 
 
@@ -400,7 +400,7 @@ def test_snug_row_aligned_blocks(case):
         ref = oracle.act(ref[None], act[0], act[1],
                          None if act[2] is None else act[2][cos],
                          None if act[3] is None else act[3][cos])[0]
-    for algo in (P.ALGO_AUTO, P.ALGO_MFMA_WIDE):
+    for algo in (P.ALGO_AUTO, P.ALGO_MFMA, P.ALGO_MFMA_WIDE):
         y = gpu_conv(g, x, f, b, act=act, algo=algo)
         got = y.reshape(B, C_out, Do * Do, 4)[bs, cos, flat]
         assert_parity(got, ref, what="algo %d" % algo)
@@ -426,7 +426,7 @@ def test_3d_wide_96_positions(g):
     cos = np.array([p[1] for p in pts])
     flat = np.array([p[2] for p in pts])
     ref = oracle.conv_points(x, f, b, g, bs, cos, flat)
-    for algo in (P.ALGO_AUTO, P.ALGO_MFMA_WIDE):
+    for algo in (P.ALGO_AUTO, P.ALGO_MFMA, P.ALGO_MFMA_WIDE):
         y = gpu_conv(g, x, f, b, algo=algo)
         got = y.reshape(B, C_out, Do ** 3, 8)[bs, cos, flat]
         assert_parity(got, ref, what="algo %d" % algo)
@@ -445,8 +445,9 @@ def test_wide_112_positions(case):
     g, C_out, D = case
     B, C_in, df = 8, 4, 3
     s, x, f, b = _case(210, g, (B, C_in, C_out, D, df))
-    y = gpu_conv(g, x, f, b, algo=P.ALGO_AUTO)
-    assert_parity(y, oracle.conv_nd(x, f, b, g), what=str(case))
+    ref = oracle.conv_nd(x, f, b, g)
+    for algo in (P.ALGO_AUTO, P.ALGO_MFMA):
+        assert_parity(gpu_conv(g, x, f, b, algo=algo), ref, what="%s algo %d" % (case, algo))
 
 
 # The 16-channel form of the 2D wide tile (one wave of channels, four of
@@ -464,7 +465,7 @@ def test_wide_16_channels(case):
     g, shape = case
     s, x, f, b = _case(220, g, shape)
     ref = oracle.conv_nd(x, f, b, g)
-    for algo in (P.ALGO_MFMA_WIDE, P.ALGO_AUTO):
+    for algo in (P.ALGO_MFMA_WIDE, P.ALGO_MFMA, P.ALGO_AUTO):
         y = gpu_conv(g, x, f, b, algo=algo)
         assert_parity(y, ref, what="%s algo %d" % (case, algo))
 
@@ -481,9 +482,9 @@ DF5_CASES = [((1, 1), (2, 8, 16, 40, 5)), ((1, -1), (1, 5, 70, 24, 5)),
              ((-1, 1), (4, 8, 8, 70, 7))]
 
 
-@pytest.mark.parametrize("algo", [P.ALGO_AUTO, P.ALGO_MFMA_WIDE, P.ALGO_MFMA_MEDIUM,
+@pytest.mark.parametrize("algo", [P.ALGO_AUTO, P.ALGO_MFMA, P.ALGO_MFMA_WIDE, P.ALGO_MFMA_MEDIUM,
                                   P.ALGO_MFMA_NARROW, P.ALGO_MFMA_TINY],
-                         ids=["auto", "wide", "medium", "narrow", "tiny"])
+                         ids=["auto", "mfma", "wide", "medium", "narrow", "tiny"])
 @pytest.mark.parametrize("case", DF5_CASES, ids=str)
 def test_2d_5x5_7x7_unrolled(case, algo):
     g, shape = case
@@ -504,7 +505,7 @@ def test_narrow_10_slots(case):
     g, shape = case
     s, x, f, b = _case(260, g, shape)
     ref = oracle.conv_nd(x, f, b, g)
-    for algo in (P.ALGO_AUTO, P.ALGO_MFMA_NARROW):
+    for algo in (P.ALGO_AUTO, P.ALGO_MFMA, P.ALGO_MFMA_NARROW):
         y = gpu_conv(g, x, f, b, algo=algo)
         assert_parity(y, ref, what="%s algo %d" % (case, algo))
 
@@ -523,7 +524,7 @@ def test_3d_8_channels(case):
     g, shape = case
     s, x, f, b = _case(240, g, shape)
     ref = oracle.conv_nd(x, f, b, g)
-    for algo in (P.ALGO_MFMA_WIDE, P.ALGO_AUTO):
+    for algo in (P.ALGO_MFMA_WIDE, P.ALGO_MFMA, P.ALGO_AUTO):
         y = gpu_conv(g, x, f, b, algo=algo)
         assert_parity(y, ref, what="%s algo %d" % (case, algo))
 
@@ -549,8 +550,9 @@ SMALL_CHANNEL_WIDTH_TILES = ["1.4.4.6", "1.4.4.4", "1.4.4.6", "1.4.4.6", "1.4.2.
 def test_small_channel_widths(case):
     g, shape = case
     s, x, f, b = _case(230, g, shape)
-    y = gpu_conv(g, x, f, b, algo=P.ALGO_AUTO)
-    assert_parity(y, oracle.conv_nd(x, f, b, g), what=str(case))
+    ref = oracle.conv_nd(x, f, b, g)
+    for algo in (P.ALGO_AUTO, P.ALGO_MFMA):
+        assert_parity(gpu_conv(g, x, f, b, algo=algo), ref, what="%s algo %d" % (case, algo))
 
 
 # The 64-position form of the 2D 64-channel wide tile (4x4 MFMA tiles per
@@ -566,8 +568,9 @@ WIDE64_CASES = [((1, 1), (1, 8, 64, 130, 3)), ((1, -1), (1, 8, 60, 130, 3)),
 def test_2d_wide_64_positions(case):
     g, shape = case
     s, x, f, b = _case(270, g, shape)
-    y = gpu_conv(g, x, f, b, algo=P.ALGO_AUTO)
-    assert_parity(y, oracle.conv_nd(x, f, b, g), what=str(case))
+    ref = oracle.conv_nd(x, f, b, g)
+    for algo in (P.ALGO_AUTO, P.ALGO_MFMA):
+        assert_parity(gpu_conv(g, x, f, b, algo=algo), ref, what="%s algo %d" % (case, algo))
 
 
 # 2D, >= 1 GFLOP, 64 output channels: the automatic choice takes the wide
@@ -589,7 +592,7 @@ def test_2d_wide_96_positions(g):
     cos = np.array([p[1] for p in pts])
     flat = np.array([p[2] for p in pts])
     ref = oracle.conv_points(x, f, b, g, bs, cos, flat)
-    for algo in (P.ALGO_AUTO, P.ALGO_MFMA_WIDE):
+    for algo in (P.ALGO_AUTO, P.ALGO_MFMA, P.ALGO_MFMA_WIDE):
         y = gpu_conv(g, x, f, b, algo=algo)
         got = y.reshape(B, C_out, Do * Do, 4)[bs, cos, flat]
         assert_parity(got, ref, what="algo %d" % algo)

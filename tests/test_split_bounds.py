@@ -1,11 +1,13 @@
 """The split-operand convolution's launches (tests/test_conv_split_gpu.py and
 the benchmark's layers), walked by the host bounds checker before any GPU sees
 them: every load, LDS slot and store of its address arithmetic
-(tests/hostcheck/check_conv_split.cpp), and the tile each layer takes.  An
-observer has to say that it knows the kernel ("kinds 7"); without, the
-automatic choice stays with the fp32 kernels, whose own tests assert them."""
+(tests/hostcheck/check_conv_split.cpp), and the tile each layer takes.  The
+layers of the other GPU tests that the automatic choice gives to the split
+kernels, and random ones, are walked too."""
 import os
 import sys
+
+import numpy as np
 
 sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
 
@@ -16,9 +18,7 @@ from test_host_bounds import conv_line  # noqa: E402
 
 
 def _run(lines):
-    out = HC.run(["kinds 7"] + lines)
-    assert out[0].startswith("ok"), out[0]
-    return out[1:]
+    return HC.run(lines)
 
 
 def test_parity_cases():
@@ -28,7 +28,7 @@ def test_parity_cases():
         f = res.split()
         assert f[0] == "ok" and f[4] == "7", (g, shape, res)
         t = f[5].split(".")
-        assert ".".join(t[2:5] + (["16"] if t[6] == "16" else [])) == tile, (g, shape, res)
+        assert ".".join(t[3:6] + (["16"] if t[7] == "16" else [])) == tile, (g, shape, res)
 
 
 def test_zero_signatures():
@@ -67,7 +67,7 @@ def test_benchmark_layers_and_sizes():
 
 def test_observer_without_the_kind():
     # a checker that cannot walk the kernel is not handed it
-    res = HC.run([conv_line(2, (1, 1), 8, 64, 64, 128, 3, P.ALGO_AUTO)])[0].split()
+    res = HC.run(["kinds 6", conv_line(2, (1, 1), 8, 64, 64, 128, 3, P.ALGO_AUTO)])[1].split()
     assert res[0] == "ok" and res[4] == "1", res
 
 
@@ -94,7 +94,56 @@ def test_linear_layers():
             if kind is not None:
                 lines.append(conv_line(len(g), g, B, ci, co, 1, 1, algo, gate))
                 want.append(kind)
-    out = HC.run(["kinds 8"] + lines)[1:]
+    out = HC.run(lines)
     for line, res, kind in zip(lines, out, want):
         f = res.split()
         assert f[0] == "ok" and f[4] == kind, (line, res, kind)
+
+
+def test_other_gpu_tests_layers():
+    # the automatic choice on the layers of the other GPU tests
+    import test_parity_gpu as T
+    lines = [conv_line(2, g, *s, P.ALGO_AUTO)
+             for g, s in T.WIDE16_CASES + T.DF5_CASES + T.NARROW10_CASES + T.SMALL_CHANNEL_WIDTH_CASES +
+             T.WIDE64_CASES]
+    lines += [conv_line(3, g, *s, P.ALGO_AUTO) for g, s in T.W3_8_CASES]
+    lines += [conv_line(2, (1, 1), *s, P.ALGO_AUTO) for s in T.WIDE_STAGE + T.ROW_BLOCKS]
+    lines += [conv_line(2, s[5], *s[:5], P.ALGO_AUTO) for s in T.SNUG]
+    lines += [conv_line(2, (1, 1), B, C, C, d, 3, P.ALGO_AUTO)
+              for B, C, d in ((2, 16, 2050), (1, 64, 2050), (1, 16, 4098), (1, 32, 3000))]
+    lines += [conv_line(1, (-1,), B, ci, co, d, 17, P.ALGO_AUTO)
+              for B, ci, co, d in ((1024, 64, 64, 60), (1000, 64, 62, 60), (1001, 64, 64, 61), (2048, 128, 128, 60))]
+    out = _run(lines)
+    for line, res in zip(lines, out):
+        assert res.startswith("ok 0 "), (line, res)
+    assert sum(res.split()[4] == "7" for res in out) >= 8
+
+
+def test_random_layers():
+    # layers of the sizes that the split kernels are for: ragged channels and
+    # positions, every signature and filter length
+    rng = np.random.default_rng(20)
+    lines = []
+    while len(lines) < 60:
+        k = int(rng.choice([1, 2, 2, 3]))
+        g = tuple(int(v) for v in rng.choice([-1, 1, 1, -1, 0], k))
+        if not any(g):
+            continue
+        df = int(rng.choice([[5, 9, 17, 30], [2, 3, 3, 4, 5, 7], [2, 3, 3, 4]][k - 1]))
+        d = df + int(np.exp(rng.uniform(np.log([16, 16, 6][k - 1]), np.log([600, 200, 30][k - 1]))))
+        ci, co = (int(np.exp(rng.uniform(np.log(24), np.log(100)))) for _ in range(2))
+        per = 2.0 * ci * co * 4 ** k * (df * (d - df + 1)) ** k  # FLOP of a batch entry
+        B = max(1, int(np.exp(rng.uniform(np.log(2e10), np.log(1.5e11))) / per))
+        if B * (ci + co) * d ** k * 2 ** k > 3e8:
+            continue
+        lines.append(conv_line(k, g, B, ci, co, d, df, P.ALGO_AUTO))
+    for _ in range(20):
+        k = int(rng.choice([1, 2, 3]))
+        n, kk = [(128, 128), (128, 64), (64, 128), (64, 256)][int(rng.integers(4))]
+        lines.append(conv_line(k, (1,) * k, int(np.exp(rng.uniform(np.log(16384), np.log(1 << 20)))),
+                               kk >> k, n >> k, 1, 1, P.ALGO_AUTO))
+    out = _run(lines)
+    for line, res in zip(lines, out):
+        assert res.startswith("ok 0 "), (line, res)
+    kinds = [res.split()[4] for res in out]
+    assert kinds.count("7") >= 25 and kinds.count("8") >= 10, kinds
