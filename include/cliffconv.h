@@ -7,7 +7,21 @@
  * linear layer of Algorithm 2, each with the bias add, the multivector
  * activation of Algorithm 3, usable on its own or fused as their epilogue,
  * and the two-layer block (convolution + activation, twice) the paper builds
- * its networks from.  All arithmetic is IEEE fp32 on the GPU.
+ * its networks from.
+ *
+ * Precision: tensors are IEEE fp32, and every product of two blades and every
+ * sum is formed to fp32 accuracy on its own; a result never depends on other
+ * blades than the product's.  Kernels on the fp32 matrix cores and vector units
+ * use IEEE fp32 products and sums.  For larger layers the automatic choice
+ * (CLIFF_ALGO_AUTO) multiplies on the bf16 matrix cores: every operand is the
+ * exact sum of three bf16 parts, a product the six largest products of parts
+ * (the rest is below 2^-24 of it), summed in fp32.  Against 64 bits its 2-norm
+ * error was 0.75 to 1.0 times that of the fp32 kernels on the layers it takes
+ * (up to 18816 products to a sum, random operands); where products are zero,
+ * which the fp32 kernels do not round, it was 1.2 (k = 1, 2) and 1.3 times (k = 3,
+ * vector-valued inputs) to 2.0 times (k = 3, inputs of one blade).  Sums that are
+ * infinite or NaN, or reach 2^96, and operands from 2^112 on are computed by fp32
+ * products.
  *
  * Algebra (paper, Background, "Clifford Algebra"): Cl_g(R^k) with signature
  * g in {-1, 0, +1}^k, generators e_1..e_k, e_i e_i = g_i, e_i e_j = -e_j e_i.
@@ -120,7 +134,9 @@ cliff_status clifford_conv_nd(int k, const int8_t* g, int64_t B, int64_t C_in,
 
 /* Kernel choice for clifford_conv_nd_algo. */
 typedef enum {
-    CLIFF_ALGO_AUTO = 0,        /* what clifford_conv_nd does */
+    CLIFF_ALGO_AUTO = 0,        /* what clifford_conv_nd does: fp32 MFMA, or bf16
+                                   MFMA with every fp32 operand as three bf16
+                                   parts where that is estimated to be faster */
     CLIFF_ALGO_DIRECT = 1,      /* one thread per output multivector, fp32 FMA */
     CLIFF_ALGO_MFMA = 2,        /* implicit GEMM on fp32 MFMA, tile shape chosen
                                    from the problem size */
@@ -215,7 +231,8 @@ cliff_status clifford_linear(int k, const int8_t* g, int64_t B, int64_t C_in,
  *   output             device [B, C_out, d_out^k, N_B]
  * Small blocks (few channels, little work) run as one fused launch that keeps
  * `mid` in on-chip memory; others as two clifford_conv_nd launches through the
- * workspace.  Both give the same results up to fp32 rounding order.
+ * workspace.  Both give the same results up to the rounding of the kernels that
+ * they run on (see Precision above).
  * Errors: as clifford_conv_nd (CLIFF_EINVAL also for a NULL workspace or
  * second filter; CLIFF_ESHAPE unless d_image >= 2 d_filter - 1); the
  * workspace and the output must not overlap each other or any input

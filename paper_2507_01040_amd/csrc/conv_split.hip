@@ -31,19 +31,20 @@
 // 16 channels of two: the lane that has (channel, position) then finds the
 // second one eight registers on.  k = 2 layers of up to 16 channels, or of a
 // last block of up to 16, ran half of their MFMAs on padding: B 8, C 16, d 258
-// 342 -> 193 us (fp32 tiles: 289).  The staging and the barrier of a step stay,
-// so wider layers keep 32.
+// 342 -> 193 us (fp32 tiles: 289; with a gate 218 and 299).  The staging and the
+// barrier of a step stay, so wider layers keep 32.
 //
 // Bound: the bf16 matrix cores at the clock their power allows.  A loop of
 // 32x32x16 MFMAs on random registers reaches 1793 TFLOP/s (2485 on zeros);
-// this kernel's MFMAs run at 1290 (k = 3, C 32, d 32) to 1500 TFLOP/s (k = 2,
-// C 64, d 128; k = 3, C 64, d 36); the rest is staging, the barrier and the
-// first fragments' reads.  Measured against the fp32 tiles: k = 2, B 8, C 64,
-// d 128, 3x3 1078 -> 601 us; k = 3, B 8, C 32, d 32 5426 -> 3550 us; C 64, d 36
-// 30.9 -> 17.8 ms; k = 1, B 4096, C 64, d 60, 17 taps 712 -> 510 us.  The error
-// against 64 bits falls from 8.6e-7 to 7.4e-7 (2-norm, 2304 products), as 16
-// products go into one rounding; where most products are zero (filters of one
-// blade) it is up to twice the fp32 tiles', six roundings to their four.
+// this kernel's MFMAs run at 1270 (k = 3, C 32, d 32) to 1460 TFLOP/s (k = 2,
+// C 64, d 128; k = 3, C 64, d 36), busy 61 to 77 % of the cycles; the rest is
+// staging, the barrier and the first fragments' reads.  Measured against the
+// fp32 tiles: k = 2, B 8, C 64, d 128, 3x3 1078 -> 615 us; k = 3, B 8, C 32, d 32
+// 5.43 -> 3.62 ms; C 64, d 36 30.9 -> 18.3 ms; k = 1, B 4096, C 64, d 60, 17 taps
+// 712 -> 516 us.  The error against 64 bits falls from 8.6e-7 to 7.4e-7 (2-norm,
+// 2304 products), as 16 products go into one rounding; where products are zero,
+// which the fp32 tiles do not round, it stays: vector-valued inputs 6.1e-7 -> 7.1e-7
+// (k = 3: 1.33 times the fp32 tiles'), inputs of one blade 1.2 to 2.0 times.
 // Tried on the 2 x 2 matrix form: 16x16x32 MFMAs with two products of parts in
 // one (2055 TFLOP/s on registers, but 28 instead of 18 KB of LDS reads a step
 // and spills: 360 -> 428 us at k = 2), a third filter slot with fragments read
@@ -52,12 +53,11 @@
 // once (360 -> 369 us).
 //
 // Values that bf16 arithmetic cannot carry (infinities, operands from 2^112 and
-// sums from 2^96 on) come out non-finite; a wave that holds such a sum computes all of
-// its sums again on the fp32 matrix cores (split_fp32_sums).  With a channel of
-// the lowest value in 7 of 8 images C 64, d 128 takes 1.79 ms (fp32 tiles 1.08;
-// with half of the images masked and one lane for an output 16.3 ms), k = 1,
-// B 1024, C 64, d 60, 17 taps 0.58 ms (0.21; 7.3), k = 3, C 32, d 32, B 2 2.8 ms
-// (1.4; 95).
+// sums from 2^96 on) come out non-finite; a wave that holds such a sum computes
+// all of its sums again on the fp32 matrix cores (split_fp32_sums).  With a channel
+// of the lowest value in all images but one C 64, d 128 takes 1.8 ms (fp32 tiles 1.1;
+// one lane for an output, half of the images masked: 16), k = 1, B 1024, C 64,
+// d 60, 17 taps 0.57 ms (0.21; 7.3), k = 3, C 32, d 32, B 2 2.8 ms (1.4; 95).
 #include <stdio.h>
 
 #include <algorithm>
@@ -68,9 +68,6 @@
 #include "epilogue.hpp"
 #include "split.hpp"
 
-#ifndef CLIFF_SPLIT_VALU
-#define CLIFF_SPLIT_VALU 6
-#endif
 namespace cliff {
 namespace {
 
@@ -386,7 +383,7 @@ __global__ __launch_bounds__(64 * WCO * WPOS, 2) void conv_split_kernel(SplitArg
             for (int i = 0; i < NM; ++i) {
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
                 if (i < nrd) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-                else if (n >= NS - 2) __builtin_amdgcn_sched_group_barrier(0x002, CLIFF_SPLIT_VALU, 0);
+                else if (n >= NS - 2) __builtin_amdgcn_sched_group_barrier(0x002, 6, 0);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
