@@ -15,18 +15,20 @@
 // and the next one's loads drain under the MFMAs.
 //
 // Measured against the fp32 kernel (linear_mfma.hip), g = (1, 1): 32 -> 32
-// channels, B = 2^20 297 -> 238 us (4.5 TB/s; a device copy of the same bytes
-// runs at 4.7), 2^18 83 -> 63, 2^16 27.6 -> 20.1 us; 64 -> 16, 2^19 160 -> 141;
-// 16 -> 32, 2^20 191 -> 182; 32 -> 16 185 -> 167.  Loads and stores of 64
+// channels, B = 2^20 297 -> 242 us (4.4 TB/s; a device copy of the same bytes
+// runs at 5.3), 2^18 81 -> 54, 2^16 29 -> 19.4 us; 64 -> 16, 2^20 308 -> 278;
+// 16 -> 32, 2^20 188 -> 187; 32 -> 16 185 -> 166; error against 64 bits 0.75 to
+// 0.98 times (signatures with two zeros) the fp32 kernel's.  Loads and stores of 64
 // contiguous bytes of 16 rows, with an exchange of lane rows behind them,
 // instead of 32 bytes of 32 rows: 277 -> 238 us.  8 groups of prefetch instead
 // of 4: 242.  64 -> 256 columns spill (8 row tiles) and stay there, as do
 // 64 -> 64, at the memory's rate already, and 256 -> 256.
 //
 // Tiles with a result that is not finite (infinities, operands from 2^112 and sums
-// from 2^96 on) are computed again on the fp32 matrix cores after the wave's last one: with a
-// channel of the lowest value in all rows 2^17 rows of 32 -> 32 channels take 96
-// us instead of 38 (half of 2^18 rows, one lane for an output: 437 us).
+// from 2^96 on) are computed again on the fp32 matrix cores after the wave's last
+// one: with a channel of the lowest value in all rows but 32, 2^17 rows of 32 -> 32
+// channels take 91 us instead of 36 (fp32 kernel 64; half of 2^18 rows masked and
+// one lane for an output: 437).
 #include <stdio.h>
 
 #include <algorithm>
