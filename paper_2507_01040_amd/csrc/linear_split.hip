@@ -248,17 +248,21 @@ __global__ __launch_bounds__(512, 2) void linear_split_kernel(LinSplitArgs a)
     }
     uint64_t bad = 0;  // bit i % 64: the wave's tile i has an infinite or NaN output
     int i = 0;
-    for (int64_t t = t0, tn; t < a.n_tile; t = tn, ++i) {
+    int64_t t = t0, tn = t + stride;
+    tile(t, tn < a.n_tile ? tn : t);
+    for (;; ++i) {
+        bad |= (uint64_t)finish(t, SPLIT_UNSCALE) << (i & 63);
+        if (tn >= a.n_tile) break;
+        t = tn;
         tn = t + stride;
         tile(t, tn < a.n_tile ? tn : t);
-        bad |= (uint64_t)finish(t, SPLIT_UNSCALE) << (i & 63);
     }
     if (bad == 0) return;
     // Those tiles (and any that share their bit) again as fp32 products on the
     // fp32 matrix cores, operands straight from memory, one input channel at a
     // time: values that bf16 parts cannot hold.
     i = 0;
-    for (int64_t t = t0; t < a.n_tile; t += stride, ++i) {
+    for (t = t0; t < a.n_tile; t += stride, ++i) {
         if (!(bad >> (i & 63) & 1)) continue;
 #pragma unroll
         for (int r = 0; r < RT; ++r)
