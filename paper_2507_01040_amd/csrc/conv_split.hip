@@ -678,15 +678,20 @@ cliff_status launch_conv_split(const ConvProblem& p, hipStream_t stream)
 {
     if (launch_observer && launch_observer->last_kind < LAUNCH_CONV_SPLIT) return CLIFF_EUNSUPPORTED;
     if (p.d_filter < 2) return CLIFF_EUNSUPPORTED;
-    // A sum's error goes with its roundings: a tap costs six here for every 16 K
-    // slots, and one on the fp32 tiles for every product that the table does not
-    // make zero.  Tables without zeros: 0.80 to 0.97 of the fp32 tiles' error
-    // (2-norm, all C_in and filters, up to 18816 products).  With zeros it is 0.87
-    // to 0.99 while there are at most 0.56 times as many roundings; past that up to
-    // 1.05 (k = 2, 3, 5 or 7 input channels; k = 3 with two zeros in g).
+    // A sum's error goes with its roundings: a tap costs six here for every 8 K
+    // slots in use (the error steps with 8, not with an MFMA's 16), and one on the
+    // fp32 tiles for every product that the table does not make zero.  Tables
+    // without zeros: 0.80 to 0.97 of the fp32 tiles' error (2-norm, all C_in and
+    // filters, up to 18816 products).  With zeros it is 0.87 to 0.995 while there are
+    // at most 1.1 times as many roundings (k = 3 tables of one zero; k = 2 with even
+    // C_in or C_in >= 11).  Past that it grows with the products of a sum: C_in 7 and
+    // 9 at k = 2 0.98 at 189 products, 1.00 at 525, 1.007 at 1029; k = 3 with two
+    // zeros 0.995 at 576, 1.05 at 7776; C_in 3 and 5 at k = 2 0.99 to 1.05.
     if (p.sign.zero) {
-        const int64_t cpg = 16 / p.nb, nz = p.nb * p.nb - __builtin_popcountll(p.sign.zero);
-        if (6.0 * (double)((p.C_in + cpg - 1) / cpg) > 0.56 * (double)p.C_in * nz / p.nb)
+        const int64_t cpc = 8 / p.nb, nz = p.nb * p.nb - __builtin_popcountll(p.sign.zero);
+        const double products = (double)p.C_in * nz / p.nb;  // of a tap
+        if (6.0 * (double)((p.C_in + cpc - 1) / cpc) > 1.1 * products &&
+            ((p.k == 2 && p.C_in < 7) || products * std::pow((double)p.d_filter, p.k) > 500.0))
             return CLIFF_EUNSUPPORTED;
     }
     // One K group with padding channels at four taps or less: the output's stores

@@ -276,9 +276,12 @@ def test_conv_split_operand_range(g, shape, ex, ew):
 # would be up to 1.05 times as far from 64 bits, and layers that do not (kind 7
 # of the launch checker).
 ZEROS = [((0, 1), (6, 3, 62, 100, 7), "1"), ((-1, 0), (6, 5, 62, 100, 7), "1"),
-         ((0, 1), (6, 7, 62, 100, 7), "1"), ((0, 0, 1), (4, 32, 30, 30, 3), "1"),
-         ((0, 1), (6, 11, 62, 100, 7), "7"), ((0, 1), (6, 8, 62, 100, 5), "7"),
-         ((1, 0, -1), (4, 16, 30, 30, 3), "7")]
+         ((0, 1), (6, 7, 62, 100, 7), "1"), ((1, 0), (6, 9, 62, 100, 7), "1"),
+         ((0, 0, 1), (4, 32, 30, 30, 3), "1"), ((0, 1), (6, 11, 62, 100, 7), "7"),
+         ((0, 1), (6, 10, 62, 100, 7), "7"), ((0, 1), (6, 13, 62, 100, 7), "7"),
+         ((1, 0, -1), (4, 16, 30, 30, 3), "7"), ((1, 0, 1), (4, 5, 30, 30, 3), "7"),
+         ((0, 1), (6, 7, 62, 100, 3), "7"), ((1, 0), (8, 9, 60, 130, 3), "7"),
+         ((0, 0, -1), (4, 4, 30, 30, 3), "7"), ((0, 0, 1), (8, 12, 60, 34, 2), "7")]
 
 
 @pytest.mark.parametrize("g,shape,kind", ZEROS, ids=str)
